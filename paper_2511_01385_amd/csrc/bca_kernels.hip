@@ -5,7 +5,7 @@
 // the two-stage dC sum (fused with dc's inverse transform).
 #include <hip/hip_runtime.h>
 
-#include "bca_kernels.hpp"
+#include "bca_block_kernels.hpp"
 
 namespace rdfft {
 
@@ -119,6 +119,19 @@ static const BcaStoreTables& store_tables(int storage) {
   return t[storage];
 }
 
+// The matrix-core kernel for a layer of p = 128 ... 1024 whose spectra of four tokens fit in
+// LDS, or nullptr.
+static BcaBwdFn block_fn(const BcaArgs& a, bool backward) {
+  static const BcaBlockTables tables[kStorages] = {bca_block_tables_f32(), bca_block_tables_bf16(),
+                                                   bca_block_tables_f16()};
+  const int logn = a.logp - 1;
+  if (logn < kBlockMinLogN || logn > kBlockMaxLogN || a.q > kBlockMaxBlocks || a.kb > kBlockMaxBlocks) return nullptr;
+  if (block_lds_bytes(logn, backward ? a.q + a.kb : std::max(a.q, a.kb), 4) > kLdsLimit) return nullptr;
+  const BcaBlockTables& t = tables[a.storage];
+  const int ig = block_groups_index(a.q), jg = block_groups_index(a.kb);
+  return backward ? t.bwd[logn - kBlockMinLogN][ig][jg] : t.fwd[logn - kBlockMinLogN][jg];
+}
+
 bool bca_shape_supported(int logp, int q, int kb, bool backward) {
   const int logn = logp - 1;
   if (logn > kBcaMaxLogN) return bca_multipass_supported(logp, q, kb, backward);
@@ -142,6 +155,7 @@ hipError_t launch_bca_forward(const BcaArgs& a, const float2* tw, hipStream_t st
     if (fn == nullptr) fn = t.sq_fwd[a.q - 1][a.logp - 1];
     if (fn != nullptr) return fn(a, tw, stream, num_cu);
   }
+  if (const BcaBwdFn fn = block_fn(a, false)) return fn(a, tw, stream, num_cu);
   return t.fwd[a.logp - 1](a, tw, stream);
 }
 
@@ -175,19 +189,20 @@ hipError_t launch_bca_backward(const BcaArgs& a, const float2* tw, hipStream_t s
   if (a.storage < 0 || a.storage >= kStorages) return hipErrorInvalidValue;
   const BcaStoreTables& t = store_tables(a.storage);
   const int64_t slots = (int64_t)a.q * a.kb * ((int64_t)1 << (a.logp - 1)) * 2;
-  // the square-layer kernels zero dc themselves (in the kernel when the dC sum is staged);
+  // the square-layer and matrix-core kernels zero dc themselves (in the kernel when the dC sum is staged);
   // every other path finds it zeroed
   BcaBwdFn sq_fn = nullptr;
   if (a.tokens > 0 && a.logp - 1 <= kBcaMaxLogN && a.q == a.kb && a.q <= kSqMaxBlocks) {
     sq_fn = t.wave_bwd[a.q - 1][a.logp - 1];
     if (sq_fn == nullptr) sq_fn = t.sq_bwd[a.q - 1][a.logp - 1];
   }
+  if (a.tokens > 0 && sq_fn == nullptr) sq_fn = block_fn(a, true);
   hipError_t e = hipSuccess;
   if (sq_fn == nullptr) {
     e = launch_fill_zero(a.dc, slots, stream);
     if (e != hipSuccess || a.tokens == 0) return e;
   }
-  // the square-layer kernels also leave dc in the time domain
+  // they also leave dc in the time domain
   if (sq_fn != nullptr) return sq_fn(a, tw, stream, num_cu);
   if (a.logp - 1 > kBcaMaxLogN) {
     e = launch_bca_multipass(a, true, tw, stream, num_cu);

@@ -310,6 +310,36 @@ def test_wave_kernel_layers(shape):
     _check(x, c, g, dtype, d, p, got, f"wave {shape}")
 
 
+# the matrix-core kernels (p = 128 ... 1024, up to 16 x 16 blocks, not the square layers of at most
+# 4 x 4): block counts that leave part of a group of four, tiles of fewer than four tokens, ragged
+# last tiles, dc by atomics and staged (2048 tokens and more; with a ragged end), dx over gy
+BLOCK = [
+    (1, 512, 1024, 128, "f32", False),
+    (3, 128, 2048, 128, "bf16", False),
+    (9, 2048, 2048, 128, "f32", True),
+    (517, 1152, 640, 128, "f16", False),
+    (6, 1280, 1280, 256, "bf16", True),
+    (5, 4096, 4096, 256, "f32", False),
+    (2, 2304, 256, 256, "f16", False),
+    (1031, 768, 1792, 256, "bf16", False),
+    (7, 4096, 4096, 512, "f32", False),
+    (11, 512, 8192, 512, "bf16", False),
+    (6, 3072, 1024, 512, "f16", False),
+    (13, 1024, 5120, 1024, "f32", False),
+    (5, 6144, 2048, 1024, "bf16", False),
+    (2050, 512, 2048, 128, "bf16", False),
+    (2048, 1024, 2048, 256, "f16", False),
+]
+
+
+@pytest.mark.parametrize("shape", BLOCK, ids=[f"T{s[0]}_{s[1]}x{s[2]}_p{s[3]}_{s[4]}{'_aliased' if s[5] else ''}" for s in BLOCK])
+def test_block_kernel_layers(shape):
+    tokens, d_in, d_out, p, dtype, alias = shape
+    x, c, g = _problem(2727 + tokens, tokens, d_in, d_out, p, 0.02, dtype)
+    got = _run(x, c, g, dtype, d_out, alias_y=alias, alias_dx=alias)
+    _check(x, c, g, dtype, d_out, p, got, f"block {shape}")
+
+
 # square layers whose dC slots exceed LDS, with dx == gy: the dC launches read gy, so they
 # must all run before the dx launch overwrites it
 SPLIT_ALIASED = [(5, 4096, 128, "bf16"), (3, 4096, 512, "f32"), (4, 4096, 512, "bf16"), (3, 8192, 1024, "bf16")]
