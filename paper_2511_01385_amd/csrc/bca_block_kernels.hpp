@@ -59,7 +59,7 @@ bca_forward_block_kernel(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c, 
   using B = BcaBlock<LOGN>;
   using In = typename St::In;
   using Out = typename St::Out;
-  constexpr int N = B::N, TPR = B::TPR, REG = B::REG, NB = B::NB, NG = WG / TPR, NW = WG / 64;
+  constexpr int N = B::N, TPR = B::TPR, REG = B::REG, NB = B::NB, NG = WG / TPR, NW = WG / 64, RPW = 64 / TPR;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (uniform: matrix instructions ignore the lane mask)
   const int grp = tid / TPR, t = tid - grp * TPR;
@@ -77,6 +77,7 @@ bca_forward_block_kernel(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c, 
 
     const int nx = TT * kb;
     for (int s0 = 0; s0 < nx; s0 += NG) {
+      if (s0 + wave * RPW >= nx) continue;  // rows synchronise at wave level: an idle wave leaves
       const int s = s0 + grp;
       const bool valid = s < nx;
       const int tt = valid ? s / kb : 0, j = valid ? s - tt * kb : 0;
@@ -85,11 +86,24 @@ bca_forward_block_kernel(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c, 
       const In src{x + ((act ? tok0 + tt : 0) * kb + j) * (int64_t)N};
       row_forward<LOGN, true>(t, act, src, LdsSpectrum{reg}, reg, tw);
     }
+    // Y_i[k] = sum_j C_ij[k] X_j[k]: rows i, columns tokens, one input block per step.  Up to 8
+    // input blocks, the C rows of the next output group are in flight while one is computed,
+    // the first group's across the barrier (more blocks do not leave the registers for that).
+    constexpr bool AHEAD = KG <= 2;
+    int u = wave / HS;
+    const int h = wave % HS;
+    typename In::raw_t raw[4 * KG];
+    auto load_c = [&](int unit, int ig) {
+      const int i = 4 * ig + n < q ? 4 * ig + n : q - 1;  // (rows past q repeat the last)
+      const int ci = i * kb * N + 16 * (unit % NB) + b;
+      static_for<4 * KG>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        raw[j] = cin.load_raw(ci + (sure(j, KG) || j < kb ? j : 0) * N);
+      });
+    };
+    if constexpr (AHEAD) load_c(u, h);
     __syncthreads();
-
-    // Y_i[k] = sum_j C_ij[k] X_j[k]: rows i, columns tokens, one input block per step
-    for (int u0 = 0; u0 < U; u0 += NW) {
-      const int u = u0 + wave / HS, h = wave % HS;
+    for (int u0 = 0; u0 < U; u0 += NW, u += NW) {
       const bool busy = u < U;
       const int g = u % NB, tg = u / NB;
       const int bin = 16 * g + b;
@@ -107,19 +121,19 @@ bca_forward_block_kernel(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c, 
       auto outputs = [&](auto s0c) {
         constexpr bool S0 = decltype(s0c)::value;
         for (int ig = h; ig < QG; ig += HS) {
-          const int i = 4 * ig + n < q ? 4 * ig + n : q - 1;  // (rows past q repeat the last)
-          const int ci = i * kb * N + bin;
-          typename In::raw_t raw[4 * KG];
-          static_for<4 * KG>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            raw[j] = cin.load_raw(ci + (sure(j, KG) || j < kb ? j : 0) * N);
-          });
+          if constexpr (!AHEAD) load_c(u, ig);
+          typename In::raw_t cur[4 * KG];
+          static_for<4 * KG>([&](auto jc) { cur[decltype(jc)::value] = raw[decltype(jc)::value]; });
+          if constexpr (AHEAD) {
+            if (ig + HS < QG) load_c(u, ig + HS);
+            else if (u + NW < U) load_c(u + NW, h);
+          }
           f32x4_t rr = {0.f, 0.f, 0.f, 0.f}, ii = rr, ir = rr, ri = rr;
           static_for<4 * KG>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
-            float2 cv = In::widen(raw[j]);
+            float2 cv = In::widen(cur[j]);
             if (!sure(j, KG) && j >= kb) cv = make_float2(0.f, 0.f);
-            const float im = S0 && b == 0 ? 0.f : cv.y;    // cross terms: none in slot 0
+            const float im = S0 && b == 0 ? 0.f : cv.y;  // cross terms: none in slot 0
             const float di = S0 && b == 0 ? cv.y : cv.x;
             rr = mfma_4x4(cv.x, X[j].x, rr);
             ii = mfma_4x4(im, X[j].y, ii);
@@ -140,6 +154,7 @@ bca_forward_block_kernel(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c, 
 
     const int ny = TT * q;
     for (int s0 = 0; s0 < ny; s0 += NG) {
+      if (s0 + wave * RPW >= ny) continue;
       const int s = s0 + grp;
       const bool valid = s < ny;
       const int tt = valid ? s / q : 0, i = valid ? s - tt * q : 0;
@@ -168,19 +183,19 @@ struct BcaBlockBwd {
 
 // Backward of one tile per turn: X_j and G_i in LDS (kb + q regions per token), dC_ij in
 // registers for all of the workgroup's tiles, dX_j over X_j.  The partial sums leave at the
-// end to `stage` (chunk float2 of them into the gy rows of each of the workgroup's first
+// end to `stage` (chunk_rows rows of dC into the gy rows of each of the workgroup's first
 // tiles, which it alone has read) or, stage == nullptr, by float32 atomics into dc.
 template <int LOGN, class St, int QG, int KG, int WG>
 __global__ void __launch_bounds__(WG)
 bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __restrict__ c, const ElemOf<St>* gy,
                           ElemOf<St>* dx, float* __restrict__ dc, int64_t tokens, int q, int kb, int TT, int TS,
-                          int64_t ntiles, float2* stage, int64_t tile_f2, int chunk, const float2* __restrict__ tw) {
+                          int64_t ntiles, float2* stage, int64_t tile_f2, int chunk_rows, const float2* __restrict__ tw) {
   using B = BcaBlock<LOGN>;
   using S = BcaBlockBwd<LOGN, QG, KG, WG>;
   using In = typename St::In;
   using Out = typename St::Out;
   constexpr int N = B::N, TPR = B::TPR, REG = B::REG, NB = B::NB, NG = WG / TPR, NW = S::NW, HS = S::HS, BT = S::BT;
-  constexpr int IGW = S::IGW, JGW = S::JGW;
+  constexpr int IGW = S::IGW, JGW = S::JGW, RPW = 64 / TPR;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (uniform: matrix instructions ignore the lane mask)
   const int grp = tid / TPR, t = tid - grp * TPR;
@@ -214,6 +229,7 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
     const int per = kb + q, ns = TT * per;
 #pragma unroll 1
     for (int s0 = 0; s0 < ns; s0 += NG) {
+      if (s0 + wave * RPW >= ns) continue;  // rows synchronise at wave level: an idle wave leaves
       const int s = s0 + grp;
       const bool valid = s < ns;
       const int tt = valid ? s / per : 0, m = valid ? s - tt * per : 0;
@@ -287,7 +303,7 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
         constexpr bool S0 = decltype(s0c)::value;
 #pragma unroll 1
         for (int jg = h; jg < (kb + 3) / 4; jg += HS) {
-          const int j = 4 * jg + n < kb ? 4 * jg + n : kb - 1;
+          const int j = 4 * jg + n < kb ? 4 * jg + n : kb - 1;  // (rows past kb repeat the last)
           const int ci = j * N + bin;
           typename In::raw_t raw[4 * QG];
           static_for<4 * QG>([&](auto ic) {
@@ -327,6 +343,7 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
     const int nx = TT * kb;
 #pragma unroll 1
     for (int s0 = 0; s0 < nx; s0 += NG) {
+      if (s0 + wave * RPW >= nx) continue;
       const int s = s0 + grp;
       const bool valid = s < nx;
       const int tt = valid ? s / kb : 0, j = valid ? s - tt * kb : 0;
@@ -339,6 +356,7 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
   }
 
   if (!dc_busy) return;
+  const float inv_rows = 1.0f / (float)chunk_rows;
   static_for<BT>([&](auto bc) {
     constexpr int bt = decltype(bc)::value;
     const int bin = 16 * (g0 + bt * NW) + b;
@@ -351,11 +369,11 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
           constexpr int r = decltype(rc)::value;
           const int i = 4 * (hi + ii * S::SI) + r;
           if (i < q && j < kb) {
-            const int e = (i * kb + j) * N + bin;
+            const int ij = i * kb + j, e = ij * N + bin;
             const float2 v = make_float2(dre[bt][ii][jj][r], dim_[bt][ii][jj][r]);
             if (stage != nullptr) {
-              const int ch = e / chunk;
-              stage[((int64_t)blockIdx.x + (int64_t)ch * gridDim.x) * tile_f2 + (e - ch * chunk)] = v;
+              const int ch = (int)(((float)ij + 0.5f) * inv_rows);  // ij / chunk_rows, exact: ij < 256
+              stage[((int64_t)blockIdx.x + (int64_t)ch * gridDim.x) * tile_f2 + (e - ch * chunk_rows * N)] = v;
             } else {
               unsafeAtomicAdd(dc + 2 * (int64_t)e, v.x);
               unsafeAtomicAdd(dc + 2 * (int64_t)e + 1, v.y);
@@ -435,9 +453,9 @@ static hipError_t bwd_block_impl(const BcaArgs& a, const float2* tw, hipStream_t
   // two-stage dC sum in consumed gy rows (dx apart from gy), as in the square-layer kernels
   const int64_t qkn = (int64_t)a.q * a.kb * N;
   const int64_t tile_f2 = (int64_t)TT * a.q * N * (int64_t)sizeof(ElemOf<St>) / (int64_t)sizeof(float2);
-  const int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(qkn, tile_f2));
-  const int64_t chunks = (qkn + chunk - 1) / chunk;
-  bool staged = a.dx != a.y && tile_f2 > 0 && 2 * qkn * grid >= kStageMinAtomics;
+  const int chunk_rows = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)a.q * a.kb, tile_f2 / N));
+  const int64_t chunks = ((int64_t)a.q * a.kb + chunk_rows - 1) / chunk_rows;
+  bool staged = a.dx != a.y && tile_f2 >= N && 2 * qkn * grid >= kStageMinAtomics;
   if (staged && chunks * grid > full) {
     // a ragged end can leave the last workgroups too few whole tiles: give their tiles to the others
     if (full / chunks >= grid - 4) grid = full / chunks;
@@ -451,10 +469,10 @@ static hipError_t bwd_block_impl(const BcaArgs& a, const float2* tw, hipStream_t
   hipLaunchKernelGGL((bca_backward_block_kernel<LOGN, St, QG, KG, WG>), dim3((unsigned)grid), dim3(WG), lds, stream,
                      static_cast<const ElemOf<St>*>(a.x), static_cast<const ElemOf<St>*>(a.c),
                      static_cast<const ElemOf<St>*>(a.y), static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, a.q, a.kb, TT,
-                     TS, tiles, stage, tile_f2, chunk, tw);
+                     TS, tiles, stage, tile_f2, chunk_rows, tw);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (staged) return launch_dc_finish(stage, a.dc, a.q * a.kb, LOGN, chunk, (int)grid, tile_f2, tw, stream);
+  if (staged) return launch_dc_finish(stage, a.dc, a.q * a.kb, LOGN, chunk_rows * N, (int)grid, tile_f2, tw, stream);
   return launch_rdfft_rows(a.dc, (int64_t)a.q * a.kb, LOGN, kStorageF32, true, tw, stream, num_cu);
 }
 
