@@ -3,12 +3,22 @@
 // Even n = 2N with N = 2^a 3^b 5^c that is not a power of two, N <= 16384.  The
 // transform is the one of the power-of-two kernels (Sec. 4.1): the N-point complex DFT of
 // z_m = x_{2m} + i x_{2m+1} followed by the post-pass that pairs bins k and N-k, and the
-// inverse pre-pass (1/n folded in) followed by the conjugate passes.  Here one workgroup
-// owns one row, keeps all N complex points in LDS, and runs a Stockham pass per radix
-// (5, 3, then 8/4/2) with the radix picked at run time; the twiddles come from the
-// hardware sine and cosine of the fraction k/M in revolutions, and a butterfly's higher
-// powers from products of its first one, so these plans need no table.
+// inverse pre-pass (1/n folded in) followed by the conjugate passes.  A row's N complex
+// points pass through LDS between Stockham passes whose radices (up to 16: the composite 6,
+// 9, 10, 12 and 15 beside the powers of two) a host plan picks at run time; the twiddles come
+// from the hardware sine and cosine of the fraction k/M in revolutions, and a butterfly's
+// higher powers from products, so these plans need no table.
+//
+// What bounds them: VALU issue in 16-bit storage, HBM in float32.  n = 6144 (16 16 12) issues 1010
+// VALU instructions per wave for 12 points a thread, 110 us of issue at 2.4 GHz for 16384 rows, and
+// takes 96 us forward and 116 us inverse in bf16 (4.2 and 3.5 TB/s), 149 us each in float32 (5.4
+// TB/s).  Radices up to 8, always 16 points per thread and the row staged through LDS before its
+// first and after its last pass (five passes, 1740 instructions for 16 points) took 200 and 208 us,
+// 231 and 192 us; 65536 rows of n = 96, each in a workgroup of its own then, 48 us against 9 us.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <vector>
 
 #include "fft_device.hpp"
 #include "launch.hpp"
@@ -18,12 +28,26 @@ namespace rdfft {
 namespace {
 
 constexpr int kMixedMaxPasses = 16;
-constexpr int kMixedMaxPerThread = 16;  // complex points per thread (N / blockDim <= 16)
+constexpr int kMixedLdsF2 = 160 * 1024 / 8;  // float2 of LDS per workgroup
 
+// One Stockham pass: butterfly j < B = N/R reads in[j + r*B], multiplies input r by
+// W_{Ns*R}^{r*k} (k = j mod Ns), runs the R-point DFT and writes out[(j/Ns)*Ns*R + k + r*Ns].
+// In LDS, every block of Ns*R outputs is followed by `pad` unused slots (element e lies at
+// e + pad*floor(e/(Ns*R))), which spreads the strided writes over the banks; as the next pass's
+// stride N/R' is a multiple of Ns*R, its reads stay at a base plus r times one step.
+struct MixedPass {
+  int R, B, Ns, pad_in, pad_out, step_in;  // step_in: LDS slots between inputs r and r+1
+  float inv_ns, inv_den;                   // 1/Ns, 1/(Ns*R)
+};
 struct MixedPlan {
-  int n_half;  // N
+  int n_half;   // N
   int passes;
-  int radix[kMixedMaxPasses];
+  int tpr;      // threads of a row
+  int log_tpr;  // of a row that shares its workgroup (a power of two), else -1
+  int rows_wg;  // rows per workgroup
+  int lds_f2;   // LDS slots of a row
+  bool deep;    // a thread holds several butterflies of a pass
+  MixedPass pass[kMixedMaxPasses];
 };
 
 // -i * a (forward) or +i * a (inverse)
@@ -33,6 +57,9 @@ __device__ __forceinline__ float2 mul_mi(float2 a) {
 }
 
 template <int R, bool INV>
+__device__ __forceinline__ void dft_any(float2* v);
+
+template <int R, bool INV>
 struct DftOdd;
 
 // 3 points: y1, y2 = (v0 - (v1+v2)/2) -+ i (sqrt(3)/2) (v1 - v2)
@@ -40,12 +67,11 @@ template <bool INV>
 struct DftOdd<3, INV> {
   __device__ __forceinline__ static void run(float2* v) {
     constexpr float s3 = 0.866025403784438646763723f;  // sin(2 pi / 3)
-    const float2 a = c_add(v[1], v[2]), b = c_scale(c_sub(v[1], v[2]), s3);
+    const float2 a = c_add(v[1], v[2]), d = mul_mi<INV>(c_sub(v[1], v[2]));
     const float2 t = make_float2(fmaf(-0.5f, a.x, v[0].x), fmaf(-0.5f, a.y, v[0].y));
     v[0] = c_add(v[0], a);
-    const float2 ib = mul_mi<INV>(b);
-    v[1] = c_add(t, ib);
-    v[2] = c_sub(t, ib);
+    v[1] = make_float2(fmaf(s3, d.x, t.x), fmaf(s3, d.y, t.y));
+    v[2] = make_float2(fmaf(-s3, d.x, t.x), fmaf(-s3, d.y, t.y));
   }
 };
 
@@ -73,138 +99,261 @@ struct DftOdd<5, INV> {
   }
 };
 
+// 9 points as 3 x 3 (n = 3 n1 + n2, k = k1 + 3 k2): W_9^{n2 k1} between the two layers
+template <bool INV>
+struct DftOdd<9, INV> {
+  __device__ __forceinline__ static void run(float2* v) {
+    // exp(-2 pi i m / 9), m = 1, 2, 4
+    constexpr float2 w1 = {0.766044443118978035202393f, -0.642787609686539326322643f};
+    constexpr float2 w2 = {0.173648177666930348851717f, -0.984807753012208059366743f};
+    constexpr float2 w4 = {-0.939692620785908384054109f, -0.342020143325668733044100f};
+    float2 u[3][3];
+    static_for<3>([&](auto n2c) {
+      constexpr int n2 = decltype(n2c)::value;
+      static_for<3>([&](auto n1c) { u[n2][decltype(n1c)::value] = v[3 * decltype(n1c)::value + n2]; });
+      DftOdd<3, INV>::run(u[n2]);
+    });
+    u[1][1] = c_mul<INV>(u[1][1], w1);
+    u[1][2] = c_mul<INV>(u[1][2], w2);
+    u[2][1] = c_mul<INV>(u[2][1], w2);
+    u[2][2] = c_mul<INV>(u[2][2], w4);
+    static_for<3>([&](auto k1c) {
+      constexpr int k1 = decltype(k1c)::value;
+      float2 w[3] = {u[0][k1], u[1][k1], u[2][k1]};
+      DftOdd<3, INV>::run(w);
+      static_for<3>([&](auto k2c) { v[k1 + 3 * decltype(k2c)::value] = w[decltype(k2c)::value]; });
+    });
+  }
+};
+
+// A*C points for coprime A and C without twiddles (Good's prime-factor mapping): input
+// n = (C n1 + A n2) mod AC; output k with k mod A = k1 and k mod C = k2.
+template <int A, int C, bool INV>
+struct DftCoprime {
+  static constexpr int out_index(int k1, int k2) {
+    for (int k = 0; k < A * C; ++k)
+      if (k % A == k1 && k % C == k2) return k;
+    return 0;
+  }
+  __device__ __forceinline__ static void run(float2* v) {
+    float2 u[C][A];
+    static_for<C>([&](auto n2c) {
+      constexpr int n2 = decltype(n2c)::value;
+      static_for<A>([&](auto n1c) {
+        constexpr int n1 = decltype(n1c)::value;
+        u[n2][n1] = v[(C * n1 + A * n2) % (A * C)];
+      });
+      // sum over n1 of W^{C n1 k} = W_A^{n1 k}: an A-point DFT in k mod A
+      dft_any<A, INV>(u[n2]);
+    });
+    static_for<A>([&](auto k1c) {
+      constexpr int k1 = decltype(k1c)::value;
+      float2 w[C];
+      static_for<C>([&](auto n2c) { w[decltype(n2c)::value] = u[decltype(n2c)::value][k1]; });
+      dft_any<C, INV>(w);
+      static_for<C>([&](auto k2c) { v[out_index(k1, decltype(k2c)::value)] = w[decltype(k2c)::value]; });
+    });
+  }
+};
+
 template <int R, bool INV>
 __device__ __forceinline__ void dft_any(float2* v) {
-  if constexpr (R == 3 || R == 5) DftOdd<R, INV>::run(v);
+  if constexpr (R == 3 || R == 5 || R == 9) DftOdd<R, INV>::run(v);
+  else if constexpr (R == 6) DftCoprime<2, 3, INV>::run(v);
+  else if constexpr (R == 10) DftCoprime<2, 5, INV>::run(v);
+  else if constexpr (R == 12) DftCoprime<4, 3, INV>::run(v);
+  else if constexpr (R == 15) DftCoprime<3, 5, INV>::run(v);
   else Dft<R, INV>::run(v);
 }
 
-// exp(-+ 2 pi i num / den) for 0 <= num < den, from the hardware sine and cosine of the
-// angle in revolutions, num / den (V_SIN_F32 / V_COS_F32 take their argument in turns, so
-// no reduction by pi is needed); the caller passes inv_den = 1/den (one division per pass,
-// not per twiddle).  Transform errors stay at 1e-7 .. 6e-7 relative (fp64 reference),
-// against 1e-7 .. 3e-7 with sincospif, whose argument reduction costs more instructions.
-template <bool INV>
-__device__ __forceinline__ float2 unit_root_dev(int num, float inv_den) {
-  const float x = (float)num * inv_den;  // revolutions
-  const float s = __builtin_amdgcn_sinf(x), c = __builtin_amdgcn_cosf(x);
-  return make_float2(c, INV ? s : -s);
+// exp(-+ 2 pi i num / den) for 0 <= num < den; the caller passes inv_den = 1/den.
+// FINE = false (16-bit rows): the hardware sine and cosine of the angle in revolutions, a few
+// 1e-7 off, a thousandth of what the rows' storage resolves.  FINE = true (float32 rows, which
+// HBM bounds): the angle is reduced to |f| <= 1/2 quarter turns in integers, so that its
+// rounding is relative to f, and Taylor sums of sine and cosine follow (remainders below 2e-9):
+// 16 instructions more per butterfly.  With the hardware functions the radix-16 plans' errors
+// were 1.4 to 1.6 times those of the radix-8 plans before them (n = 6144: 6.7e-7 against 4.3e-7),
+// as a butterfly's fifteenth power carries fifteen times its first one's error.
+template <bool INV, bool FINE>
+__device__ __forceinline__ float2 unit_root_dev(int num, int den, float inv_den) {
+  if constexpr (!FINE) {
+    const float x = (float)num * inv_den;  // revolutions
+    const float s = __builtin_amdgcn_sinf(x), c = __builtin_amdgcn_cosf(x);
+    return make_float2(c, INV ? s : -s);
+  } else {
+    const int q = (int)rintf((float)(4 * num) * inv_den);  // nearest quarter turn
+    const float f = (float)(4 * num - q * den) * inv_den;  // the rest, in quarter turns
+    const float z = f * f;
+    // sin and cos of f pi/2: (pi/2)^k / k! with alternating signs
+    const float s = f * fmaf(z, fmaf(z, fmaf(z, fmaf(z, 1.60441184787359822e-4f, -4.68175413531868810e-3f),
+                                             7.96926262461670452e-2f), -6.45964097506246253e-1f), 1.57079632679489662f);
+    const float c = fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, -2.52020423730606055e-5f, 9.19260274839426581e-4f),
+                                                 -2.08634807633529609e-2f), 2.53669507901048014e-1f),
+                                 -1.23370055013616983f), 1.0f);
+    const bool odd = (q & 1) != 0;
+    const float x = odd ? s : c, y = odd ? c : s;
+    const uint32_t flip_x = (uint32_t)((q + 1) & 2) << 30, flip_y = (uint32_t)((q & 2) ^ (INV ? 0 : 2)) << 30;
+    return make_float2(__uint_as_float(__float_as_uint(x) ^ flip_x), __uint_as_float(__float_as_uint(y) ^ flip_y));
+  }
 }
 
-// One Stockham pass of radix R over the row in LDS: butterfly j < B = N/R reads
-// in[j + r*B], multiplies input r by W_{Ns*R}^{r*k} (k = j mod Ns), runs the R-point DFT
-// and writes out[(j/Ns)*Ns*R + k + r*Ns].  All reads of the pass precede its writes.  A
-// thread's butterflies are T apart, so their k follow from the first one by adding T mod Ns
-// (no division per butterfly).  (Padding the row as the power-of-two kernels do made these
-// passes slower: their strides are multiples of 3 and 5.)
-template <int R, bool INV>
-__device__ __forceinline__ void mixed_pass(float2* lds, int N, int Ns) {
-  constexpr int MB = (kMixedMaxPerThread + R - 1) / R;  // butterflies per thread, at most
-  const int B = N / R, T = blockDim.x, t = threadIdx.x;
+// Pairs of the pre-pass whose loads a thread has in flight at a time: one pair at a time left the
+// inverse waiting for HBM (n = 6144 bf16, 16384 rows: 160 us; 116 us with four).  The forward's
+// post-pass reads LDS and gained nothing from it.
+constexpr int kMixedAhead = 4;
+
+// Butterflies of one pass that a thread can hold: one, or (deep plans, T = 1024 threads) up to
+// ceil(16384 / (1024 R))
+template <int R, bool DEEP>
+constexpr int mixed_butterflies() {
+  return DEEP ? (16 + R - 1) / R : 1;
+}
+
+// read(r-th input position) / write as functors of an LDS slot or global pair index; a pass
+// that reads or writes LDS on both sides has a barrier between its reads and its writes.
+template <int R, bool INV, bool DEEP, bool FROM_GLOBAL, bool TO_GLOBAL, class Acc>
+__device__ __forceinline__ void mixed_pass(const MixedPass& p, int t, int tpr, bool active, float2* lds, const Acc& acc) {
+  constexpr int MB = mixed_butterflies<R, DEEP>();
+  constexpr bool FINE = std::is_same<typename Acc::raw_t, float2>::value;
   float2 v[MB][R];
+  int kk[MB], qq[MB];
 #pragma unroll
   for (int s = 0; s < MB; ++s) {
-    const int j = t + s * T;
-    if (j < B) {
+    const int j = t + s * tpr;
+    // j / Ns: exact, as (j + 1/2) / Ns stays 1/(2 Ns) away from any integer and j < 2^14
+    qq[s] = FROM_GLOBAL ? j : (int)(((float)j + 0.5f) * p.inv_ns);
+    kk[s] = FROM_GLOBAL ? 0 : j - qq[s] * p.Ns;
+    if (j < p.B) {
+      if constexpr (FROM_GLOBAL) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[s][r] = lds[j + r * B];
+        for (int r = 0; r < R; ++r) v[s][r] = acc.load(j + r * p.B);
+      } else {
+        const float2* in = lds + j + qq[s] * p.pad_in;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[s][r] = in[r * p.step_in];
+      }
     }
   }
-  __syncthreads();
-  const float inv_den = 1.0f / (float)(Ns * R);
-  const int step = T % Ns;
-  int k = t % Ns;  // k of butterfly t + s*T, advanced by step per s
+  if constexpr (!FROM_GLOBAL) __syncthreads();
 #pragma unroll
   for (int s = 0; s < MB; ++s) {
-    const int j = t + s * T;
-    if (s > 0) {
-      k += step;
-      if (k >= Ns) k -= Ns;
-    }
-    if (j < B) {
-      if (Ns > 1) {
-        const float2 w1 = unit_root_dev<INV>(k, inv_den);
-        float2 w = w1;
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-          v[s][r] = c_mul<false>(v[s][r], w);
-          if (r + 1 < R) w = c_mul<false>(w, w1);
+    const int j = t + s * tpr;
+    if (j < p.B) {
+      if constexpr (!FROM_GLOBAL) {
+        if (p.Ns > 1) {
+          // powers of the butterfly's twiddle, each from its halves
+          float2 w[R];
+          w[1] = unit_root_dev<INV, FINE>(kk[s], p.Ns * R, p.inv_den);
+          static_for<R - 1>([&](auto rc) {
+            constexpr int r = decltype(rc)::value + 1;
+            if constexpr (r > 1) w[r] = c_mul<false>(w[r / 2], w[r - r / 2]);
+            v[s][r] = c_mul<false>(v[s][r], w[r]);
+          });
         }
       }
       dft_any<R, INV>(v[s]);
-      const int o = (j - k) * R + k;
+      const int o = (j - kk[s]) * R + kk[s];
+      if constexpr (TO_GLOBAL) {
+        if (active) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) lds[o + r * Ns] = v[s][r];
+          for (int r = 0; r < R; ++r) acc.store(o + r * p.Ns, v[s][r]);
+        }
+      } else {
+        float2* out = lds + o + qq[s] * p.pad_out;
+#pragma unroll
+        for (int r = 0; r < R; ++r) out[FROM_GLOBAL ? r : r * p.Ns] = v[s][r];
+      }
     }
   }
-  __syncthreads();
+  if constexpr (!TO_GLOBAL) __syncthreads();
 }
 
-template <bool INV>
-__device__ __forceinline__ void mixed_passes(float2* lds, const MixedPlan& plan) {
-  int Ns = 1;
-  for (int q = 0; q < plan.passes; ++q) {
-    const int R = plan.radix[q];
-    switch (R) {
-      case 2: mixed_pass<2, INV>(lds, plan.n_half, Ns); break;
-      case 3: mixed_pass<3, INV>(lds, plan.n_half, Ns); break;
-      case 4: mixed_pass<4, INV>(lds, plan.n_half, Ns); break;
-      case 5: mixed_pass<5, INV>(lds, plan.n_half, Ns); break;
-      default: mixed_pass<8, INV>(lds, plan.n_half, Ns); break;
-    }
-    Ns *= R;
+template <bool INV, bool DEEP, bool FROM_GLOBAL, bool TO_GLOBAL, class Acc>
+__device__ __forceinline__ void mixed_pass_any(const MixedPass& p, int t, int tpr, bool active, float2* lds,
+                                               const Acc& acc) {
+  switch (p.R) {
+    case 2: mixed_pass<2, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 3: mixed_pass<3, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 4: mixed_pass<4, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 5: mixed_pass<5, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 6: mixed_pass<6, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 8: mixed_pass<8, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 9: mixed_pass<9, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 10: mixed_pass<10, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 12: mixed_pass<12, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 15: mixed_pass<15, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    default: mixed_pass<16, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
   }
 }
 
+// A workgroup owns rows_wg rows of tpr threads each.  The forward's first pass reads the row
+// from global memory and its post-pass writes it; the inverse's pre-pass reads it and its
+// last pass writes it.  Every load of a row precedes its first store (barriers between).
 // HC: the spectrum (the forward's output, the inverse's input) in the halfcomplex layout.
-template <class Acc, class Elem, bool INV, bool HC>
-__global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, MixedPlan plan) {
+template <class Acc, class Elem, bool INV, bool HC, bool DEEP>
+__global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, int64_t rows, MixedPlan plan) {
   extern __shared__ float2 mixed_lds[];
-  const int N = plan.n_half, T = blockDim.x, t = threadIdx.x;
-  Elem* const rp = buf + (int64_t)blockIdx.x * N;
-  const Acc sig{rp};                                   // the signal pairs (x_{2m}, x_{2m+1})
+  constexpr bool FINE = std::is_same<typename Acc::raw_t, float2>::value;
+  const int N = plan.n_half, T = plan.tpr;
+  const int rho = plan.log_tpr >= 0 ? (int)threadIdx.x >> plan.log_tpr : 0;
+  const int t = (int)threadIdx.x - rho * T;
+  const int64_t row = (int64_t)blockIdx.x * plan.rows_wg + rho;
+  const bool active = row < rows;
+  float2* const lds = mixed_lds + (size_t)rho * plan.lds_f2;
+  Elem* const rp = buf + (active ? row : 0) * (int64_t)N;
+  const Acc sig{rp};                                // the signal pairs (x_{2m}, x_{2m+1})
   const auto spec = spectrum_view<HC, Acc>(rp, N);  // the packed spectrum
   if constexpr (!INV) {
-    for (int m = t; m < N; m += T) mixed_lds[m] = sig.load(m);
-  } else {
-    // pre-pass: Z~_m = (s + i conj(W_n^m) d) / n, Z~_{N-m} = conj(s - i conj(W_n^m) d) / n with
-    // s = Y_m + conj(Y_{N-m}), d = Y_m - conj(Y_{N-m}); slot 0 holds (Y_0, Y_{n/2})
-    const float sc = 1.0f / (2.0f * N), inv_n = 1.0f / (float)(2 * N);
-    for (int m = t; 2 * m <= N; m += T) {
-      const float2 ya = spec.load(m);
-      if (m == 0) {
-        mixed_lds[0] = make_float2(sc * (ya.x + ya.y), sc * (ya.x - ya.y));
-        continue;
-      }
-      const float2 yb = c_conj(spec.load(N - m));
-      const float2 s = c_add(ya, yb), d = c_sub(ya, yb);
-      const float2 w = unit_root_dev<true>(m, inv_n);         // conj(W_n^m)
-      const float2 q = c_mul<false>(d, make_float2(-sc * w.y, sc * w.x));  // i conj(W_n^m) d / n
-      mixed_lds[m] = make_float2(fmaf(s.x, sc, q.x), fmaf(s.y, sc, q.y));
-      if (2 * m != N) mixed_lds[N - m] = make_float2(fmaf(s.x, sc, -q.x), -fmaf(s.y, sc, -q.y));
-    }
-  }
-  __syncthreads();
-  mixed_passes<INV>(mixed_lds, plan);
-  if constexpr (!INV) {
+    mixed_pass_any<INV, DEEP, true, false>(plan.pass[0], t, T, active, lds, sig);
+    for (int q = 1; q < plan.passes; ++q) mixed_pass_any<INV, DEEP, false, false>(plan.pass[q], t, T, active, lds, sig);
+    if (!active) return;
     // post-pass: Y_k = s/2 + (-i W_n^k / 2) d, Y_{N-k} = conj(s/2 - (-i W_n^k / 2) d) with
     // s = Z_k + conj(Z_{N-k}), d = Z_k - conj(Z_{N-k}); slot 0 = (Y_0, Y_{n/2})
     const float inv_n = 1.0f / (float)(2 * N);
     for (int k = t; 2 * k <= N; k += T) {
-      const float2 a = mixed_lds[k];
+      const float2 a = lds[k];
       if (k == 0) {
         spec.store(0, make_float2(a.x + a.y, a.x - a.y));
         continue;
       }
-      const float2 b = c_conj(mixed_lds[N - k]);
+      const float2 b = c_conj(lds[N - k]);
       const float2 s = c_add(a, b), d = c_sub(a, b);
-      const float2 w = unit_root_dev<false>(k, inv_n);  // W_n^k
+      const float2 w = unit_root_dev<false, FINE>(k, 2 * N, inv_n);  // W_n^k
       const float2 q = c_mul<false>(d, make_float2(0.5f * w.y, -0.5f * w.x));  // -i W_n^k d / 2
       spec.store(k, make_float2(fmaf(s.x, 0.5f, q.x), fmaf(s.y, 0.5f, q.y)));
       if (2 * k != N) spec.store(N - k, make_float2(fmaf(s.x, 0.5f, -q.x), -fmaf(s.y, 0.5f, -q.y)));
     }
   } else {
-    for (int m = t; m < N; m += T) sig.store(m, mixed_lds[m]);
+    // pre-pass: Z~_m = (s + i conj(W_n^m) d) / n, Z~_{N-m} = conj(s - i conj(W_n^m) d) / n with
+    // s = Y_m + conj(Y_{N-m}), d = Y_m - conj(Y_{N-m}); slot 0 holds (Y_0, Y_{n/2})
+    const float sc = 1.0f / (2.0f * N), inv_n = 1.0f / (float)(2 * N);
+    for (int m0 = t; 2 * m0 <= N; m0 += kMixedAhead * T) {
+      typename Acc::raw_t ra[kMixedAhead], rb[kMixedAhead];
+      static_for<kMixedAhead>([&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        const int m = m0 + u * T;
+        const bool in = 2 * m <= N;
+        ra[u] = spec.load_raw(in ? m : 0);
+        rb[u] = spec.load_raw(in && m != 0 ? N - m : 0);
+      });
+      static_for<kMixedAhead>([&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        const int m = m0 + u * T;
+        if (2 * m <= N) {
+          const float2 ya = Acc::widen(ra[u]), yb = c_conj(Acc::widen(rb[u]));
+          const float2 s = c_add(ya, yb), d = c_sub(ya, yb);
+          const float2 w = unit_root_dev<true, FINE>(m, 2 * N, inv_n);         // conj(W_n^m)
+          const float2 q = c_mul<false>(d, make_float2(-sc * w.y, sc * w.x));  // i conj(W_n^m) d / n
+          const float2 lo = make_float2(fmaf(s.x, sc, q.x), fmaf(s.y, sc, q.y));
+          lds[m] = m == 0 ? make_float2(sc * (ya.x + ya.y), sc * (ya.x - ya.y)) : lo;
+          if (m != 0 && 2 * m != N) lds[N - m] = make_float2(fmaf(s.x, sc, -q.x), -fmaf(s.y, sc, -q.y));
+        }
+      });
+    }
+    __syncthreads();
+    for (int q = 0; q + 1 < plan.passes; ++q)
+      mixed_pass_any<INV, DEEP, false, false>(plan.pass[q], t, T, active, lds, sig);
+    mixed_pass_any<INV, DEEP, false, true>(plan.pass[plan.passes - 1], t, T, active, lds, sig);
   }
 }
 
@@ -214,46 +363,137 @@ hipError_t allow_lds(K kernel) {
                              160 * 1024);
 }
 
-template <class Acc, class Elem, bool INV, bool HC>
-hipError_t launch_mixed(void* buf, int64_t rows, const MixedPlan& plan, int threads, hipStream_t stream) {
-  static const hipError_t attr = allow_lds(mixed_rows_kernel<Acc, Elem, INV, HC>);
+template <class Acc, class Elem, bool INV, bool HC, bool DEEP>
+hipError_t launch_mixed_t(void* buf, int64_t rows, const MixedPlan& plan, hipStream_t stream) {
+  static const hipError_t attr = allow_lds(mixed_rows_kernel<Acc, Elem, INV, HC, DEEP>);
   if (attr != hipSuccess) return attr;
-  const size_t lds = (size_t)plan.n_half * sizeof(float2);
+  const int threads = plan.tpr * plan.rows_wg;
+  const size_t lds = (size_t)plan.lds_f2 * plan.rows_wg * sizeof(float2);
   Elem* base = static_cast<Elem*>(buf);
-  const int64_t max_rows = kMaxGridThreads / threads;
+  const int64_t max_rows = kMaxGridThreads / threads * plan.rows_wg;
   for (int64_t r0 = 0; r0 < rows; r0 += max_rows) {
     const int64_t nr = std::min<int64_t>(max_rows, rows - r0);
-    hipLaunchKernelGGL((mixed_rows_kernel<Acc, Elem, INV, HC>), dim3((unsigned)nr), dim3(threads), lds, stream,
-                       base + r0 * plan.n_half, plan);
+    hipLaunchKernelGGL((mixed_rows_kernel<Acc, Elem, INV, HC, DEEP>),
+                       dim3((unsigned)((nr + plan.rows_wg - 1) / plan.rows_wg)), dim3(threads), lds, stream,
+                       base + r0 * plan.n_half, nr, plan);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
+template <class Acc, class Elem, bool INV, bool HC>
+hipError_t launch_mixed(void* buf, int64_t rows, const MixedPlan& plan, hipStream_t stream) {
+  return plan.deep ? launch_mixed_t<Acc, Elem, INV, HC, true>(buf, rows, plan, stream)
+                   : launch_mixed_t<Acc, Elem, INV, HC, false>(buf, rows, plan, stream);
+}
 
-// Radices of N = 2^a 3^b 5^c: fives, threes, then eights and one four or two
+constexpr int kMixedRadices[] = {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
+
+// VALU instructions of a radix-R butterfly: its DFT, R-1 twiddle products and the R-2 powers
+// they need, and its LDS addresses, plus the fixed cost of a pass per butterfly
+double butterfly_cost(int R) {
+  static const double dft[17] = {0, 0, 4, 14, 16, 36, 40, 0, 52, 100, 92, 0, 104, 0, 0, 178, 148};
+  return dft[R] + 8.0 * (R - 1) + 2.0 * R + 30.0;
+}
+
+// The cheapest factorisation of m into radices no larger than kMixedRadices[from] (largest first)
+void best_radices(int n_half, int m, int from, double cost, std::vector<int>* cur, std::vector<int>* best,
+                  double* best_cost) {
+  if (cost >= *best_cost) return;
+  if (m == 1) {
+    *best = *cur;
+    *best_cost = cost;
+    return;
+  }
+  for (int i = from; i < (int)(sizeof(kMixedRadices) / sizeof(int)); ++i) {
+    const int R = kMixedRadices[i];
+    if (m % R != 0) continue;
+    cur->push_back(R);
+    best_radices(n_half, m / R, i, cost + (double)(n_half / R) * butterfly_cost(R), cur, best, best_cost);
+    cur->pop_back();
+  }
+}
+
+// The plan of N = 2^a 3^b 5^c.  Radices: the cheapest factorisation by VALU instructions.  An
+// odd radix comes first when there is one (its outputs, R apart, then need no padding), the
+// others in falling order.  Threads: one butterfly each in the pass with the most of them (a
+// wave without a butterfly only waits at the barriers), up to 1024; short rows share a workgroup.
 bool make_plan(int64_t n_half, MixedPlan* plan) {
   if (n_half < 1 || n_half > kMixedMaxHalf || (n_half & (n_half - 1)) == 0) return false;
-  int64_t m = n_half;
-  int q = 0;
-  auto push = [&](int r) {
-    if (q >= kMixedMaxPasses) return false;
-    plan->radix[q++] = r;
-    m /= r;
-    return true;
-  };
-  while (m % 5 == 0)
-    if (!push(5)) return false;
-  while (m % 3 == 0)
-    if (!push(3)) return false;
-  while (m % 8 == 0)
-    if (!push(8)) return false;
-  if (m == 4 && !push(4)) return false;
-  if (m == 2 && !push(2)) return false;
+  int m = (int)n_half;
+  for (int f : {2, 3, 5})
+    while (m % f == 0) m /= f;
   if (m != 1) return false;
-  plan->n_half = (int)n_half;
-  plan->passes = q;
+  const int N = (int)n_half;
+  std::vector<int> cur, radices;
+  double cost = 1e30;
+  best_radices(N, N, 0, 0.0, &cur, &radices, &cost);
+  if (radices.empty() || (int)radices.size() > kMixedMaxPasses) return false;
+  for (size_t i = 0; i < radices.size(); ++i)
+    if (radices[i] & 1) {
+      std::swap(radices[0], radices[i]);
+      break;
+    }
+  plan->n_half = N;
+  plan->passes = (int)radices.size();
+  int Ns = 1, pad_in = 0, max_b = 0, lds = N;
+  for (int q = 0; q < plan->passes; ++q) {
+    MixedPass& p = plan->pass[q];
+    const int R = radices[q], M = Ns * R;
+    p.R = R;
+    p.B = N / R;
+    p.Ns = Ns;
+    p.inv_ns = 1.0f / (float)Ns;
+    p.inv_den = 1.0f / (float)M;
+    p.pad_in = pad_in;
+    p.step_in = p.B + pad_in * (p.B / Ns);
+    // the writes of neighbouring lanes: runs of Ns slots M apart.  Sixteen lanes cover 16 slots of
+    // two banks each: with M + pad = Ns (mod 16) the runs follow one another on the banks
+    int pad = 0;
+    if (q + 1 < plan->passes && Ns < 16) {
+      pad = (((Ns - M) % 16) + 16) % 16;
+      if (pad * 8 > M) pad = M % 2 == 0 ? 1 : 0;
+      if (Ns == 1) pad = R % 2 == 0 ? 1 : 0;
+      if (N + pad * (N / M) > kMixedLdsF2) pad = 0;
+    }
+    p.pad_out = pad_in = pad;
+    lds = std::max(lds, N + pad * (N / M));
+    max_b = std::max(max_b, p.B);
+    Ns = M;
+  }
+  plan->lds_f2 = lds;
+  int tpr = 1;
+  if (max_b <= 128) {
+    while (tpr < max_b) tpr *= 2;
+  } else {
+    tpr = std::min(1024, (max_b + 63) / 64 * 64);
+  }
+  plan->tpr = tpr;
+  plan->rows_wg = 1;
+  while (plan->rows_wg * 2 * tpr <= 256 && plan->rows_wg * 2 * lds <= kMixedLdsF2 / 4) plan->rows_wg *= 2;
+  plan->log_tpr = -1;
+  if (plan->rows_wg > 1)
+    for (plan->log_tpr = 0; (1 << plan->log_tpr) < tpr;) ++plan->log_tpr;
+  plan->deep = max_b > tpr;
   return true;
+}
+
+// The plans of all supported lengths, made once
+const MixedPlan* find_plan(int64_t n_half) {
+  static const std::vector<MixedPlan> plans = [] {
+    std::vector<MixedPlan> v;
+    for (int64_t h = 1; h <= kMixedMaxHalf; ++h) {
+      int64_t m = h;
+      for (int f : {2, 3, 5})
+        while (m % f == 0) m /= f;
+      MixedPlan p;
+      if (m == 1 && make_plan(h, &p)) v.push_back(p);
+    }
+    return v;
+  }();
+  const auto it = std::lower_bound(plans.begin(), plans.end(), n_half,
+                                   [](const MixedPlan& p, int64_t h) { return p.n_half < h; });
+  return it != plans.end() && it->n_half == n_half ? &*it : nullptr;
 }
 
 // In-place pairs <-> halfcomplex conversion of one row per workgroup (the permutation of
@@ -309,24 +549,22 @@ hipError_t launch_mixed_layout_t(void* buf, int64_t rows, int n_half, int thread
   return hipSuccess;
 }
 
+// threads of a converter's workgroup: about 16 slots each
 int threads_for(int64_t n_half) {
-  // n_half / threads <= kMixedMaxPerThread bounds every pass's butterflies per thread
   return (int)std::min<int64_t>(1024, std::max<int64_t>(64, ((n_half + 16 * 64 - 1) / (16 * 64)) * 64));
 }
 
 }  // namespace
 
 bool mixed_length_supported(int64_t n) {
-  MixedPlan p;
-  return n % 2 == 0 && make_plan(n / 2, &p);
+  return n % 2 == 0 && find_plan(n / 2) != nullptr;
 }
 
 hipError_t launch_mixed_rows(void* buf, int64_t rows, int64_t n, int storage, bool inv, bool halfcomplex,
                              hipStream_t stream) {
-  MixedPlan plan;
-  if (!make_plan(n / 2, &plan)) return hipErrorInvalidValue;
-  const int threads = threads_for(n / 2);
-  using Fn = hipError_t (*)(void*, int64_t, const MixedPlan&, int, hipStream_t);
+  const MixedPlan* plan = find_plan(n / 2);
+  if (plan == nullptr) return hipErrorInvalidValue;
+  using Fn = hipError_t (*)(void*, int64_t, const MixedPlan&, hipStream_t);
   static const Fn table[2][3][2] = {
       {{&launch_mixed<GlobalF32, float2, false, false>, &launch_mixed<GlobalF32, float2, true, false>},
        {&launch_mixed<GlobalBF16, uint32_t, false, false>, &launch_mixed<GlobalBF16, uint32_t, true, false>},
@@ -334,7 +572,7 @@ hipError_t launch_mixed_rows(void* buf, int64_t rows, int64_t n, int storage, bo
       {{&launch_mixed<GlobalF32, float2, false, true>, &launch_mixed<GlobalF32, float2, true, true>},
        {&launch_mixed<GlobalBF16, uint32_t, false, true>, &launch_mixed<GlobalBF16, uint32_t, true, true>},
        {&launch_mixed<GlobalF16, uint32_t, false, true>, &launch_mixed<GlobalF16, uint32_t, true, true>}}};
-  return table[halfcomplex ? 1 : 0][storage][inv ? 1 : 0](buf, rows, plan, threads, stream);
+  return table[halfcomplex ? 1 : 0][storage][inv ? 1 : 0](buf, rows, *plan, stream);
 }
 
 }  // namespace rdfft
@@ -343,8 +581,7 @@ namespace rdfft {
 
 hipError_t launch_mixed_layout(void* buf, int64_t rows, int64_t n, bool half16, bool to_halfcomplex,
                                hipStream_t stream) {
-  MixedPlan plan;
-  if (!make_plan(n / 2, &plan)) return hipErrorInvalidValue;
+  if (!mixed_length_supported(n)) return hipErrorInvalidValue;
   using Fn = hipError_t (*)(void*, int64_t, int, int, hipStream_t);
   static const Fn table[2][2] = {
       {&launch_mixed_layout_t<float2, float, false>, &launch_mixed_layout_t<float2, float, true>},

@@ -191,6 +191,28 @@ def test_mixed_radix_parity(n, dtype):
     assert_close(to_host_f64(t), ord_.rdfft_inverse(inputs.to_f64(y, dtype)), dtype, f"mixed inverse n={n} {dtype}")
 
 
+# plans of every radix (n = 18: a single 9; 50, 250, 31250: fives alone), rows that share a workgroup
+# with a partial last one, a thread with several butterflies (n = 31250, 32400), both layouts
+@pytest.mark.parametrize("dtype,n,rows", [("f32", 18, 1), ("bf16", 24, 70), ("f32", 50, 33), ("f16", 108, 65),
+                                          ("f32", 180, 31), ("bf16", 250, 7), ("f32", 324, 3), ("f32", 1500, 5),
+                                          ("f16", 1536, 3), ("bf16", 7500, 3), ("f32", 31250, 2), ("bf16", 32400, 2)])
+def test_mixed_radix_plans(dtype, n, rows):
+    x = inputs.normal_rows(_seed(n, dtype, 9), rows, n, dtype)
+    t = to_device(x, dtype)
+    hc = t.clone()
+    api.rdfft_forward(t)
+    torch.cuda.synchronize()
+    assert_close(to_host_f64(t), ord_.rdfft_forward(inputs.to_f64(x, dtype)), dtype, f"mixed forward n={n} {dtype}")
+    api.rdfft_forward_halfcomplex(hc)
+    assert torch.equal(hc, api.rdfft_pairs_to_halfcomplex(t.clone()))
+    back = api.rdfft_inverse_halfcomplex(hc)
+    spec = to_host_f64(t)
+    api.rdfft_inverse(t)
+    torch.cuda.synchronize()
+    assert torch.equal(back, t)
+    assert_close(to_host_f64(t), ord_.rdfft_inverse(spec), dtype, f"mixed inverse n={n} {dtype}")
+
+
 @pytest.mark.parametrize("n", [30, 3000, 32000])
 def test_mixed_radix_guard_bands_and_round_trip(n):
     rows, pad = 5, 1024
