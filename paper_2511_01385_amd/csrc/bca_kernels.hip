@@ -81,6 +81,33 @@ static hipError_t dc_finish_launch(const FinishPtrs<MAXB>& fp, int count, int ro
   return hipGetLastError();
 }
 
+// The second stage for layers of few, long rows: their units are too few to fill the chip and
+// each thread would wait on many slots' loads in turn (one circulant of p = 8192: 16 units, 16.8
+// us).  Here 64 slots go to a workgroup, whose four waves sum a quarter of the partials each, the
+// sum is stored over dc, and the row kernel inverts it.
+constexpr int kSumSlots = 64, kSumWaves = 4;
+__global__ void __launch_bounds__(kSumSlots * kSumWaves)
+    bca_dc_sum_kernel(const float2* __restrict__ stage, float* __restrict__ dc, int slots, int chunk, int groups,
+                      int64_t tile_f2) {
+  __shared__ float2 part[kSumWaves][kSumSlots];
+  const int s = threadIdx.x % kSumSlots, w = threadIdx.x / kSumSlots;
+  const int e = blockIdx.x * kSumSlots + s;
+  float2 v = make_float2(0.f, 0.f);
+  if (e < slots) {
+    const int ch = e / chunk;
+    const float2* p = stage + (int64_t)ch * groups * tile_f2 + (e - ch * chunk);
+#pragma unroll 16
+    for (int b = w; b < groups; b += kSumWaves) v = c_add(v, p[b * tile_f2]);
+  }
+  part[w][s] = v;
+  __syncthreads();
+  if (w == 0 && e < slots) {
+    for (int o = 1; o < kSumWaves; ++o) v = c_add(v, part[o][s]);
+    reinterpret_cast<float2*>(dc)[e] = v;
+  }
+}
+constexpr int kSumMaxUnits = 32;  // units of the finish kernel below which the sum kernel is used
+
 template <int MAXB, int... L>
 static std::array<hipError_t (*)(const FinishPtrs<MAXB>&, int, int, int, int, int64_t, const float2*, hipStream_t),
                   sizeof...(L)>
@@ -92,6 +119,14 @@ hipError_t launch_dc_finish(const float2* stage, float* dc, int rows_ij, int log
                             int64_t tile_f2, const float2* tw, hipStream_t stream) {
   static const auto tab = dc_finish_table<1>(std::make_integer_sequence<int, kBcaMaxLogN + 1>{});
   if (logn < 0 || logn > kBcaMaxLogN) return hipErrorInvalidValue;
+  if (rows_ij * ((groups + kReduceGroup - 1) / kReduceGroup) < kSumMaxUnits) {
+    const int slots = rows_ij << logn;
+    hipLaunchKernelGGL(bca_dc_sum_kernel, dim3((unsigned)((slots + kSumSlots - 1) / kSumSlots)),
+                       dim3(kSumSlots * kSumWaves), 0, stream, stage, dc, slots, chunk, groups, tile_f2);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_rdfft_rows(dc, rows_ij, logn, kStorageF32, true, tw, stream, 0);
+  }
   const FinishPtrs<1> fp{{stage}, {dc}};
   return tab[logn](fp, 1, rows_ij, chunk, groups, tile_f2, tw, stream);
 }
