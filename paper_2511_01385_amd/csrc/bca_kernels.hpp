@@ -398,7 +398,22 @@ struct BcaSq {
   static constexpr int NSL = QB * JPT;        // (i, j) slots per bin per thread
 };
 
-template <int LOGN, class St, int QB, int WG = BcaPlan<LOGN>::BWD_WG>
+// Threads of the square-layer backward: the plan's, or 1024 where a thread of 512 would hold too
+// many slots.  Held to 128 registers, 16 values a thread then spill unless the twiddle reads are
+// kept inside the loop (below): so layers that fit 512 threads keep them (p = 2048, 2 x 2 blocks:
+// 59 us against 63 us), and 4 x 4 blocks of 2048, which else went to the general kernel, take
+// 176 us instead of 416 us (bf16, 4096 tokens).
+constexpr int kSqMaxSlots = 16;  // C and dC values per thread: bins per thread * q * kb
+template <int LOGN, int QB>
+constexpr int sq_bwd_wg() {
+  constexpr int wg = BcaPlan<LOGN>::BWD_WG;
+  if constexpr (wg == 1024 || BcaPlan<LOGN>::TPR < 64) return wg;
+  using S = BcaSq<LOGN, QB, wg>;
+  using S2 = BcaSq<LOGN, QB, 1024>;
+  return S::BT * S::NSL > kSqMaxSlots && S2::BT * S2::NSL <= kSqMaxSlots && BcaPlan<LOGN>::N <= 1024 ? 1024 : wg;
+}
+
+template <int LOGN, class St, int QB, int WG = sq_bwd_wg<LOGN, QB>()>
 __global__ void __launch_bounds__(WG) bca_backward_sq_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __restrict__ c,
                                                                       const ElemOf<St>* gy, ElemOf<St>* dx, float* __restrict__ dc,
                                                                       int64_t tokens, int tt_per_tile, int64_t ntiles,
@@ -447,6 +462,8 @@ __global__ void __launch_bounds__(WG) bca_backward_sq_kernel(const ElemOf<St>* _
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t tok0 = tile * TT;
     const int nvalid = (int)(tokens - tok0 < TT ? tokens - tok0 : TT);
+    const float2* twg = tw;
+    if constexpr (WG == 1024 && B::P::E == 16) asm volatile("" : "+s"(twg));  // twiddles read anew per tile
 
     // Phase A: X_j = rdFFT(x_j), G_i = rdFFT(g_i)
     const int nx = TT * QB, ns = 2 * TT * QB;
@@ -459,7 +476,7 @@ __global__ void __launch_bounds__(WG) bca_backward_sq_kernel(const ElemOf<St>* _
       const bool act = valid && tt < nvalid;
       const ElemOf<St>* base = s < nx ? x : gy;
       const ElemOf<St>* srcp = base + ((act ? tok0 + tt : 0) * QB + j) * (int64_t)N;
-      row_forward<LOGN, true>(t, act, In{srcp}, LdsSpectrum{reg}, reg, tw);
+      row_forward<LOGN, true>(t, act, In{srcp}, LdsSpectrum{reg}, reg, twg);
     }
     __syncthreads();
 
@@ -501,7 +518,7 @@ __global__ void __launch_bounds__(WG) bca_backward_sq_kernel(const ElemOf<St>* _
       const bool act = valid && tt < nvalid;
       float2* reg = valid ? xs + (size_t)s * REG : dummy;
       const Out dst{dx + ((act ? tok0 + tt : 0) * QB + j) * (int64_t)N};
-      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, tw);
+      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, twg);
     }
     __syncthreads();
   }
@@ -696,7 +713,6 @@ static hipError_t bwd_impl(const BcaArgs& a, const float2* tw, hipStream_t strea
 
 // Square layers with few blocks: register-resident C and dC (bca_backward_sq_kernel)
 constexpr int kSqMaxBlocks = 4;  // q == kb <= 4
-constexpr int kSqMaxSlots = 16;  // C and dC values per thread: bins per thread * q * kb
 
 // Tokens per tile of the square-layer kernels: the largest TT (at most 64 and the token
 // count) whose TT*rpt spectra, plus a spare region when TT*QB transforms leave some of
@@ -752,13 +768,13 @@ static hipError_t fwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t st
 
 template <int LOGN, int QB>
 constexpr bool sq_fits() {
-  using S = BcaSq<LOGN, QB, BcaPlan<LOGN>::BWD_WG>;
+  using S = BcaSq<LOGN, QB, sq_bwd_wg<LOGN, QB>()>;
   return S::BT * S::NSL <= kSqMaxSlots && S::TS <= 8;  // short rows: many threads per bin
 }
 
 template <int LOGN, class St, int QB>
 static hipError_t bwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu) {
-  constexpr int WG = BcaPlan<LOGN>::BWD_WG;
+  constexpr int WG = sq_bwd_wg<LOGN, QB>();
   using S = BcaSq<LOGN, QB, WG>;
   bool spare = false;
   const int TT = sq_tokens_per_tile(LOGN, 2 * QB, QB, WG / BcaPlan<LOGN>::TPR, a.tokens, kLdsLimit, &spare);

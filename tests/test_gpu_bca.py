@@ -58,6 +58,9 @@ SMALL = [
     # a token's spectra beyond the forward's two-workgroups-per-CU budget (8 x 8 blocks of 1024)
     (3, 8192, 8192, 1024, "bf16"),
     (2, 8192, 8192, 1024, "f32"),
+    # square layers whose backward takes 1024 threads to hold its slots
+    (9, 8192, 8192, 2048, "f32"),
+    (5, 6144, 6144, 2048, "f16"),
 ]
 
 
