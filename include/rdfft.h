@@ -177,6 +177,16 @@ RDFFT_API int bca_backward(const void *x, const void *c_spectra, void *gy, bca_g
                  int64_t d_out, int64_t p, int64_t tokens, rdfft_dtype_t dtype, rdfft_stream_t stream);
 
 /*
+ * bca_backward_keep -- bca_backward that only reads gy, for a caller whose upstream gradient
+ * must survive and who would else pass a copy of it.  dx must not overlap gy; gy may
+ * share memory with x.  p up to 8192 (longer blocks transform gy in place:
+ * RDFFT_EUNSUPPORTED).  dc is always summed with float32 atomics (the staging of partial
+ * sums that bca_backward does in gy is not open to it).  Otherwise as bca_backward.
+ */
+RDFFT_API int bca_backward_keep(const void *x, const void *c_spectra, const void *gy, bca_grads_t *grads, int64_t d_in,
+                 int64_t d_out, int64_t p, int64_t tokens, rdfft_dtype_t dtype, rdfft_stream_t stream);
+
+/*
  * bca_forward_batched / bca_backward_batched -- `count` independent layers of one shape
  * (the same d_in, d_out, p, tokens and dtype, each with its own tensors), such as the query
  * and value adapters of every layer of an encoder (Sec. 5.1.2), in one call.  Square layers

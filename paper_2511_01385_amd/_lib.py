@@ -31,6 +31,7 @@ EXPORTS = (
     "rdfft_inverse_halfcomplex",
     "bca_forward",
     "bca_backward",
+    "bca_backward_keep",
     "bca_forward_batched",
     "bca_backward_batched",
     "rdfft_init",
@@ -61,7 +62,7 @@ def load() -> ctypes.CDLL:
         f = getattr(lib, name)
         f.argtypes = [vp, i64, i64, i32, vp]
         f.restype = i32
-    for name in ("bca_forward", "bca_backward"):
+    for name in ("bca_forward", "bca_backward", "bca_backward_keep"):
         f = getattr(lib, name)
         f.argtypes = [vp, vp, vp, ctypes.POINTER(BcaGrads), i64, i64, i64, i64, i32, vp]
         f.restype = i32

@@ -20,14 +20,21 @@ class RdfftError(RuntimeError):
         self.status = status
 
 
+_CODES = {torch.float32: _lib.RDFFT_F32, torch.bfloat16: _lib.RDFFT_BF16, torch.float16: _lib.RDFFT_F16}
+
+# The current device and its current stream as plain integers.  The public calls build a Stream
+# object each time (3 us of a call that takes 9 us on the host with a 5 us kernel); they
+# serve where this torch has no raw ones.
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return _lib.RDFFT_F32
-    if t.dtype == torch.bfloat16:
-        return _lib.RDFFT_BF16
-    if t.dtype == torch.float16:
-        return _lib.RDFFT_F16
-    raise TypeError(f"rdfft supports float32, bfloat16 and float16 storage, got {t.dtype}")
+    code = _CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"rdfft supports float32, bfloat16 and float16 storage, got {t.dtype}")
+    return code
 
 
 def _dev(t: torch.Tensor, name: str) -> int:
@@ -39,10 +46,11 @@ def _dev(t: torch.Tensor, name: str) -> int:
 
 
 def _stream(t: torch.Tensor) -> int:
-    if t.device.index is not None and t.device.index != torch.cuda.current_device():
+    device = t.get_device()
+    if device != _current_device():
         # the library works on the current device
-        raise ValueError(f"tensor on {t.device}, current device is cuda:{torch.cuda.current_device()}")
-    return torch.cuda.current_stream(t.device).cuda_stream
+        raise ValueError(f"tensor on {t.device}, current device is cuda:{_current_device()}")
+    return _raw_stream(device)
 
 
 def _check(status: int, what: str) -> None:
@@ -111,17 +119,28 @@ def _layer_shapes(x: torch.Tensor, c_spectra: torch.Tensor, out: torch.Tensor, o
     if c_spectra.dim() != 3:
         raise ValueError(f"c_spectra must have shape (q, kb, p), got {tuple(c_spectra.shape)}")
     q, kb, p = c_spectra.shape
-    if x.dim() != 2 or x.shape[1] != kb * p:
-        raise ValueError(f"x must have shape (tokens, {kb * p}), got {tuple(x.shape)}")
-    tokens = x.shape[0]
-    if tuple(out.shape) != (tokens, q * p):
+    xs = x.shape
+    if len(xs) != 2 or xs[1] != kb * p:
+        raise ValueError(f"x must have shape (tokens, {kb * p}), got {tuple(xs)}")
+    tokens = xs[0]
+    if out.shape != (tokens, q * p):
         raise ValueError(f"{out_name} must have shape ({tokens}, {q * p}), got {tuple(out.shape)}")
-    for name, t in (("c_spectra", c_spectra), (out_name, out)):
-        if t.dtype != x.dtype:
-            raise TypeError(f"{name} is {t.dtype}, x is {x.dtype}")
-        if t.device != x.device:
-            raise ValueError(f"{name} is on {t.device}, x on {x.device}")
+    dtype, device = x.dtype, x.get_device()
+    if c_spectra.dtype != dtype or out.dtype != dtype or c_spectra.get_device() != device or out.get_device() != device:
+        for name, t in (("c_spectra", c_spectra), (out_name, out)):
+            if t.dtype != dtype:
+                raise TypeError(f"{name} is {t.dtype}, x is {dtype}")
+            if t.device != x.device:
+                raise ValueError(f"{name} is on {t.device}, x on {x.device}")
     return q, kb, p, tokens
+
+
+def _grad_shapes(x: torch.Tensor, dx: torch.Tensor, dc: torch.Tensor, cshape) -> None:
+    """Refuses a dx unlike x, and a dc that is not float32 of the spectra's shape on x's device."""
+    if dx.shape != x.shape or dx.dtype != x.dtype or dx.get_device() != x.get_device():
+        raise ValueError(f"dx must match x: {tuple(x.shape)} {x.dtype} on {x.device}")
+    if dc.shape != cshape or dc.get_device() != x.get_device():
+        raise ValueError(f"dc must have shape {tuple(cshape)} on {x.device}, got {tuple(dc.shape)}")
 
 
 def bca_forward(x: torch.Tensor, c_spectra: torch.Tensor, y: torch.Tensor) -> torch.Tensor:
@@ -141,33 +160,47 @@ def bca_backward(x: torch.Tensor, c_spectra: torch.Tensor, gy: torch.Tensor, dx:
     ``gy`` is left unspecified; ``dx`` may be ``gy`` itself when d_in == d_out (for blocks
     beyond 8192, with at most 8 blocks per row).
     """
+    return _backward("bca_backward", x, c_spectra, gy, dx, dc)
+
+
+def bca_backward_keep(x: torch.Tensor, c_spectra: torch.Tensor, gy: torch.Tensor, dx: torch.Tensor, dc: torch.Tensor):
+    """``bca_backward`` that leaves ``gy`` as it was: ``dx`` apart from it, blocks of at most 8192."""
+    return _backward("bca_backward_keep", x, c_spectra, gy, dx, dc)
+
+
+def _backward(name, x, c_spectra, gy, dx, dc):
     q, kb, p, tokens = _layer_shapes(x, c_spectra, gy, "gy")
-    if tuple(dx.shape) != tuple(x.shape) or dx.dtype != x.dtype or dx.device != x.device:
-        raise ValueError(f"dx must match x: {tuple(x.shape)} {x.dtype} on {x.device}")
-    if tuple(dc.shape) != (q, kb, p) or dc.device != x.device:
-        raise ValueError(f"dc must have shape ({q}, {kb}, {p}) on {x.device}, got {tuple(dc.shape)}")
+    _grad_shapes(x, dx, dc, (q, kb, p))
     if dc.dtype != torch.float32:
         raise TypeError("dc is float32")
     grads = _lib.BcaGrads(_dev(dx, "dx"), _dev(dc, "dc"))
-    st = _lib.load().bca_backward(
+    st = getattr(_lib.load(), name)(
         _dev(x, "x"), _dev(c_spectra, "c_spectra"), _dev(gy, "gy"), ctypes.byref(grads),
         kb * p, q * p, p, tokens, _code(x), _stream(x),
     )
-    _check(st, "bca_backward")
+    _check(st, name)
     return dx, dc
 
 
 def _pointer_array(ts, name):
-    return (ctypes.c_void_p * len(ts))(*[_dev(t, f"{name}[{i}]") for i, t in enumerate(ts)])
+    if not all([t.is_cuda and t.is_contiguous() for t in ts]):
+        for i, t in enumerate(ts):
+            _dev(t, f"{name}[{i}]")  # raises for the first that is not
+    return (ctypes.c_void_p * len(ts))(*[t.data_ptr() for t in ts])
 
 
 def _batch_shapes(xs, cs, outs, out_name):
     if not (len(xs) == len(cs) == len(outs)):
         raise ValueError("one x, c_spectra and output per layer")
-    shapes = {_layer_shapes(x, c, o, out_name) for x, c, o in zip(xs, cs, outs)}
-    if len(shapes) != 1 or len({x.dtype for x in xs}) != 1 or len({x.device for x in xs}) != 1:
-        raise ValueError("the layers of a batch share one shape, storage type and device")
-    return shapes.pop()
+    first = _layer_shapes(xs[0], cs[0], outs[0], out_name)
+    dtype, device = xs[0].dtype, xs[0].get_device()
+    xshape, cshape, oshape = xs[0].shape, cs[0].shape, outs[0].shape
+    for x, c, o in zip(xs, cs, outs):
+        if (x.shape != xshape or c.shape != cshape or o.shape != oshape or x.dtype != dtype or c.dtype != dtype
+                or o.dtype != dtype or x.get_device() != device or c.get_device() != device or o.get_device() != device):
+            _layer_shapes(x, c, o, out_name)  # a layer that does not agree with itself has its own message
+            raise ValueError("the layers of a batch share one shape, storage type and device")
+    return first
 
 
 def bca_forward_batched(xs, c_spectras, ys):
@@ -190,12 +223,14 @@ def bca_backward_batched(xs, c_spectras, gys, dxs, dcs):
     q, kb, p, tokens = _batch_shapes(xs, c_spectras, gys, "gy")
     if not (len(dxs) == len(dcs) == len(xs)):
         raise ValueError("one dx and dc per layer")
+    x0 = xs[0]
+    shape, dtype, device, cshape = x0.shape, x0.dtype, x0.get_device(), c_spectras[0].shape
     for x, dx, dc in zip(xs, dxs, dcs):
-        if tuple(dx.shape) != tuple(x.shape) or dx.dtype != x.dtype or dx.device != x.device:
+        if dx.shape != shape or dx.dtype != dtype or dx.get_device() != device:
             raise ValueError(f"dx must match x: {tuple(x.shape)} {x.dtype} on {x.device}")
-        if tuple(dc.shape) != (q, kb, p) or dc.device != x.device or dc.dtype != torch.float32:
+        if dc.shape != cshape or dc.get_device() != device or dc.dtype != torch.float32:
             raise ValueError(f"dc must be float32 of shape ({q}, {kb}, {p}) on {x.device}")
-    grads = (_lib.BcaGrads * len(xs))(*[_lib.BcaGrads(_dev(dx, "dx"), _dev(dc, "dc")) for dx, dc in zip(dxs, dcs)])
+    grads = (_lib.BcaGrads * len(xs))(*zip(_pointer_array(dxs, "dx"), _pointer_array(dcs, "dc")))
     st = _lib.load().bca_backward_batched(
         len(xs), _pointer_array(xs, "x"), _pointer_array(c_spectras, "c_spectra"), _pointer_array(gys, "gy"), grads,
         kb * p, q * p, p, tokens, _code(xs[0]), _stream(xs[0]),

@@ -455,7 +455,7 @@ static hipError_t bwd_block_impl(const BcaArgs& a, const float2* tw, hipStream_t
   const int64_t tile_f2 = (int64_t)TT * a.q * N * (int64_t)sizeof(ElemOf<St>) / (int64_t)sizeof(float2);
   const int chunk_rows = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)a.q * a.kb, tile_f2 / N));
   const int64_t chunks = ((int64_t)a.q * a.kb + chunk_rows - 1) / chunk_rows;
-  bool staged = a.dx != a.y && tile_f2 >= N && 2 * qkn * grid >= kStageMinAtomics;
+  bool staged = a.dx != a.y && !a.keep_gy && tile_f2 >= N && 2 * qkn * grid >= kStageMinAtomics;
   if (staged && chunks * grid > full) {
     // a ragged end can leave the last workgroups too few whole tiles: give their tiles to the others
     if (full / chunks >= grid - 4) grid = full / chunks;

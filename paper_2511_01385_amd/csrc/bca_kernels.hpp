@@ -797,7 +797,7 @@ static hipError_t bwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t st
   const int64_t chunks = (QKN + chunk - 1) / chunk;
   // (worth a second launch only when the atomics it replaces are many: 4.2M float32 atomics
   // for the 4096-wide layer took ~24 us, 0.6M for the 768-wide one less than the launch)
-  const bool staged = a.dx != a.y && tile_bytes % (int64_t)sizeof(float2) == 0 && chunks * grid <= a.tokens / TT &&
+  const bool staged = a.dx != a.y && !a.keep_gy && tile_bytes % (int64_t)sizeof(float2) == 0 && chunks * grid <= a.tokens / TT &&
                       2 * (int64_t)QKN * grid >= kStageMinAtomics;
   float2* const stage = staged ? static_cast<float2*>(a.y) : nullptr;
   if (!staged) {  // the kernel's atomics add into dc
@@ -1148,7 +1148,7 @@ static hipError_t bwd_wave_launch(const WavePtrs<St, MAXB>& ptrs, int count, boo
   const int64_t groups = (tokens + TW - 1) / TW;
   // one workgroup per CU in all: fewer workgroups, fewer dC partial sums to add
   const int64_t grid = std::max<int64_t>(1, std::min<int64_t>((groups + NW - 1) / NW, num_cu / count));
-  // Two-stage dC sum when dx has its own buffer (apart): workgroup b's first groups are the
+  // Two-stage dC sum when dx has its own buffer and gy may be written (apart): workgroup b's first groups are the
   // tokens [b*NW*TW, (b+1)*NW*TW), whose gy rows only it reads; once all its waves are
   // done it writes its partial sums there (QKN float2 must fit those rows, all of them
   // valid tokens)
@@ -1189,7 +1189,7 @@ template <int LOGN, class St, int QB>
 static hipError_t bwd_wave_impl(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu) {
   const WavePtrs<St, 1> p{{static_cast<const ElemOf<St>*>(a.x)}, {static_cast<const ElemOf<St>*>(a.c)},
                           {static_cast<ElemOf<St>*>(a.y)}, {static_cast<ElemOf<St>*>(a.dx)}, {a.dc}};
-  return bwd_wave_launch<LOGN, St, QB, 1>(p, 1, a.dx != a.y, a.tokens, tw, stream, num_cu);
+  return bwd_wave_launch<LOGN, St, QB, 1>(p, 1, a.dx != a.y && !a.keep_gy, a.tokens, tw, stream, num_cu);
 }
 
 // Batches: kMaxBatch-wide pointer lists, count layers in grid rows

@@ -8,7 +8,9 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
+#include <functional>
 #include <mutex>
 #include <vector>
 
@@ -165,16 +167,17 @@ int check_forward_alias(const void* x, const void* y, int64_t d_in, int64_t d_ou
   return RDFFT_OK;
 }
 
-// bca_backward's checks beyond check_bca
+// bca_backward's checks beyond check_bca; keep: gy is only read (it may share memory with x, and
+// dx may not be it)
 int check_backward_grads(const void* x, const void* c_spectra, const void* gy, const void* dx, const float* dc,
-                         int64_t d_in, int64_t d_out, int64_t p, int64_t tokens, const BcaShape& sh) {
+                         int64_t d_in, int64_t d_out, int64_t p, int64_t tokens, const BcaShape& sh, bool keep = false) {
   if (dc == nullptr || !aligned16(dc)) return RDFFT_EINVAL;
   if (overlaps(dc, sh.dc_bytes, c_spectra, sh.c_bytes)) return RDFFT_EINVAL;
   if (tokens > 0) {
     if (dx == nullptr || !aligned16(dx)) return RDFFT_EINVAL;
-    if (overlaps(x, sh.x_bytes, gy, sh.y_bytes)) return RDFFT_EINVAL;
+    if (!keep && overlaps(x, sh.x_bytes, gy, sh.y_bytes)) return RDFFT_EINVAL;
     if (overlaps(dx, sh.x_bytes, x, sh.x_bytes) || overlaps(dx, sh.x_bytes, c_spectra, sh.c_bytes)) return RDFFT_EINVAL;
-    if (dx == gy) {
+    if (dx == gy && !keep) {
       if (d_in != d_out) return RDFFT_EINVAL;
       if (p > 8192 && sh.q > rdfft::kMpMaxInPlaceBlocks) return RDFFT_EUNSUPPORTED;
     } else if (overlaps(dx, sh.x_bytes, gy, sh.y_bytes)) {
@@ -187,19 +190,46 @@ int check_backward_grads(const void* x, const void* c_spectra, const void* gy, c
   return RDFFT_OK;
 }
 
+int backward(const void* x, const void* c_spectra, void* gy, const bca_grads_t* grads, int64_t d_in, int64_t d_out,
+             int64_t p, int64_t tokens, int dtype, rdfft_stream_t stream, bool keep) {
+  if (grads == nullptr) return RDFFT_EINVAL;
+  BcaShape sh;
+  int st = check_bca(x, c_spectra, gy, d_in, d_out, p, tokens, dtype, true, &sh);
+  if (st != RDFFT_OK) return st;
+  float* dc = grads->dc;
+  void* dx = grads->dx;
+  st = check_backward_grads(x, c_spectra, gy, dx, dc, d_in, d_out, p, tokens, sh, keep);
+  if (st != RDFFT_OK) return st;
+  if (keep && p > 8192) return RDFFT_EUNSUPPORTED;
+  const float2* tw = nullptr;
+  int num_cu = 0;
+  st = ensure_device(&tw, &num_cu);
+  if (st != RDFFT_OK) return st;
+  rdfft::BcaArgs a{x, c_spectra, gy, dx, dc, tokens, sh.q, sh.kb, sh.logp, dtype, keep};
+  return rdfft::launch_bca_backward(a, tw, reinterpret_cast<hipStream_t>(stream), num_cu) == hipSuccess
+             ? RDFFT_OK
+             : RDFFT_ELAUNCH;
+}
+
 // Layers of a batch: nothing one layer writes may overlap anything of another layer (reads
 // may share buffers, e.g. one x for several layers).
 struct Span {
   const void* p;
   int64_t bytes;
   bool written;
+  int layer;
 };
-bool batch_disjoint(const std::vector<std::vector<Span>>& layers) {
-  for (size_t a = 0; a < layers.size(); ++a)
-    for (size_t b = a + 1; b < layers.size(); ++b)
-      for (const Span& u : layers[a])
-        for (const Span& v : layers[b])
-          if ((u.written || v.written) && overlaps(u.p, u.bytes, v.p, v.bytes)) return false;
+bool batch_disjoint(std::vector<Span>& spans) {
+  // in order of address, a span can only overlap the following ones that start before it ends
+  std::sort(spans.begin(), spans.end(),
+            [](const Span& a, const Span& b) { return std::less<const void*>()(a.p, b.p); });
+  for (size_t a = 0; a < spans.size(); ++a) {
+    const uintptr_t end = reinterpret_cast<uintptr_t>(spans[a].p) + (uintptr_t)spans[a].bytes;
+    for (size_t b = a + 1; b < spans.size() && reinterpret_cast<uintptr_t>(spans[b].p) < end; ++b)
+      if (spans[a].layer != spans[b].layer && (spans[a].written || spans[b].written) &&
+          overlaps(spans[a].p, spans[a].bytes, spans[b].p, spans[b].bytes))
+        return false;
+  }
   return true;
 }
 
@@ -254,22 +284,13 @@ int bca_forward(const void* x, const void* c_spectra, void* y, bca_grads_t* grad
 
 int bca_backward(const void* x, const void* c_spectra, void* gy, bca_grads_t* grads, int64_t d_in, int64_t d_out,
                  int64_t p, int64_t tokens, rdfft_dtype_t dtype, rdfft_stream_t stream) {
-  if (grads == nullptr) return RDFFT_EINVAL;
-  BcaShape sh;
-  int st = check_bca(x, c_spectra, gy, d_in, d_out, p, tokens, dtype, true, &sh);
-  if (st != RDFFT_OK) return st;
-  float* dc = grads->dc;
-  void* dx = grads->dx;
-  st = check_backward_grads(x, c_spectra, gy, dx, dc, d_in, d_out, p, tokens, sh);
-  if (st != RDFFT_OK) return st;
-  const float2* tw = nullptr;
-  int num_cu = 0;
-  st = ensure_device(&tw, &num_cu);
-  if (st != RDFFT_OK) return st;
-  rdfft::BcaArgs a{x, c_spectra, gy, dx, dc, tokens, sh.q, sh.kb, sh.logp, dtype};
-  return rdfft::launch_bca_backward(a, tw, reinterpret_cast<hipStream_t>(stream), num_cu) == hipSuccess
-             ? RDFFT_OK
-             : RDFFT_ELAUNCH;
+  return backward(x, c_spectra, gy, grads, d_in, d_out, p, tokens, dtype, stream, false);
+}
+
+int bca_backward_keep(const void* x, const void* c_spectra, const void* gy, bca_grads_t* grads, int64_t d_in,
+                      int64_t d_out, int64_t p, int64_t tokens, rdfft_dtype_t dtype, rdfft_stream_t stream) {
+  // (BcaArgs has one pointer for y and gy; with keep_gy no kernel writes through it)
+  return backward(x, c_spectra, const_cast<void*>(gy), grads, d_in, d_out, p, tokens, dtype, stream, true);
 }
 
 int bca_forward_batched(int count, const void* const* x, const void* const* c_spectra, void* const* y, int64_t d_in,
@@ -278,7 +299,8 @@ int bca_forward_batched(int count, const void* const* x, const void* const* c_sp
   if (count == 0) return RDFFT_OK;
   if (x == nullptr || c_spectra == nullptr || y == nullptr) return RDFFT_EINVAL;
   BcaShape sh;
-  std::vector<std::vector<Span>> spans((size_t)count);
+  std::vector<Span> spans;
+  spans.reserve((size_t)count * 5);
   for (int b = 0; b < count; ++b) {
     int st = check_bca(x[b], c_spectra[b], y[b], d_in, d_out, p, tokens, dtype, false, &sh);
     if (st != RDFFT_OK) return st;
@@ -286,7 +308,7 @@ int bca_forward_batched(int count, const void* const* x, const void* const* c_sp
       st = check_forward_alias(x[b], y[b], d_in, d_out, p, sh);
       if (st != RDFFT_OK) return st;
     }
-    spans[b] = {{x[b], sh.x_bytes, false}, {c_spectra[b], sh.c_bytes, false}, {y[b], sh.y_bytes, true}};
+    spans.insert(spans.end(), {{x[b], sh.x_bytes, false, b}, {c_spectra[b], sh.c_bytes, false, b}, {y[b], sh.y_bytes, true, b}});
   }
   if (tokens == 0) return RDFFT_OK;
   if (!batch_disjoint(spans)) return RDFFT_EINVAL;
@@ -324,18 +346,19 @@ int bca_backward_batched(int count, const void* const* x, const void* const* c_s
   if (x == nullptr || c_spectra == nullptr || gy == nullptr || grads == nullptr) return RDFFT_EINVAL;
   BcaShape sh;
   bool apart = true;  // every layer's dx apart from its gy
-  std::vector<std::vector<Span>> spans((size_t)count);
+  std::vector<Span> spans;
+  spans.reserve((size_t)count * 5);
   for (int b = 0; b < count; ++b) {
     int st = check_bca(x[b], c_spectra[b], gy[b], d_in, d_out, p, tokens, dtype, true, &sh);
     if (st != RDFFT_OK) return st;
     st = check_backward_grads(x[b], c_spectra[b], gy[b], grads[b].dx, grads[b].dc, d_in, d_out, p, tokens, sh);
     if (st != RDFFT_OK) return st;
     apart = apart && grads[b].dx != gy[b];
-    spans[b] = {{x[b], sh.x_bytes, false},
-                {c_spectra[b], sh.c_bytes, false},
-                {gy[b], sh.y_bytes, true},
-                {grads[b].dx, tokens > 0 ? sh.x_bytes : 0, true},
-                {grads[b].dc, sh.dc_bytes, true}};
+    spans.insert(spans.end(), {{x[b], sh.x_bytes, false, b},
+                               {c_spectra[b], sh.c_bytes, false, b},
+                               {gy[b], sh.y_bytes, true, b},
+                               {grads[b].dx, tokens > 0 ? sh.x_bytes : 0, true, b},
+                               {grads[b].dc, sh.dc_bytes, true, b}});
   }
   if (!batch_disjoint(spans)) return RDFFT_EINVAL;
   const float2* tw = nullptr;

@@ -52,6 +52,7 @@ struct BcaArgs {
   int64_t tokens;
   int q, kb, logp;    // p = 2^logp
   int storage;        // kStorageF32, kStorageBF16 or kStorageF16
+  bool keep_gy = false;  // backward: y is read only (no staging of dC sums in it; p <= 8192, dx apart)
 };
 
 hipError_t launch_bca_forward(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu);

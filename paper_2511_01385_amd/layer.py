@@ -9,9 +9,9 @@ All arithmetic on the data runs in the library's kernels; torch only allocates
 buffers, casts the parameter and reshapes.
 
 Memory: the forward keeps x and the packed spectra (q*kb*p storage elements) for the
-backward, nothing else.  The backward needs one buffer of the upstream gradient's size,
-which the library uses as work space and then fills with dx (allowed when
-d_in == d_out, and for blocks longer than 8192 when there are at most 8 of them per
+backward, nothing else.  The backward allocates dx and, for blocks of at most 8192, nothing
+more: the library only reads the upstream gradient.  Longer blocks need a copy of it as
+work space, which dx then shares (when d_in == d_out and there are at most 8 blocks per
 row; otherwise dx gets its own buffer).  With ``clobber_grad=True`` it works
 in the upstream gradient tensor itself instead of a copy, as the paper does
 ("overwriting the grad_output", Sec. 5.1.1); only do that when nothing else reads
@@ -45,15 +45,22 @@ class _BcaFunction(torch.autograd.Function):
     def backward(ctx, gy: torch.Tensor):
         x2d, spectra = ctx.saved_tensors
         q, kb, p = spectra.shape
+        given = gy
         gy = gy.contiguous()
         if gy.dtype != x2d.dtype:
             gy = gy.to(x2d.dtype)
-        elif not ctx.clobber_grad:
+        dc = torch.empty((q, kb, p), dtype=torch.float32, device=x2d.device)
+        mine = ctx.clobber_grad or gy.data_ptr() != given.data_ptr()  # may be overwritten
+        if not mine and p <= 8192 and gy.data_ptr() % 16 == 0:
+            # the library only reads the upstream gradient
+            dx = torch.empty_like(x2d)
+            api.bca_backward_keep(x2d, spectra, gy, dx, dc)
+            return dx, dc, None, None
+        if not mine:
             gy = gy.clone()  # the library overwrites it
         # dx may share the work buffer when the layer is square (for blocks beyond 8192, when
         # a per-bin product holds its q blocks)
         dx = gy if q == kb and (p <= 8192 or q <= 8) else torch.empty_like(x2d)
-        dc = torch.empty((q, kb, p), dtype=torch.float32, device=x2d.device)
         api.bca_backward(x2d, spectra, gy, dx, dc)
         return dx, dc, None, None
 

@@ -203,6 +203,20 @@ def test_bca_batched_validation(lib):
     assert lib.bca_backward_batched(2, xs, cs, gys, None, d, d, p, t, F32, None) == EINVAL
 
 
+def test_bca_backward_keep_validation(lib):
+    """gy is only read: it may share memory with x, dx may not be it, and long blocks are refused."""
+    d, p, t = 256, 64, 8
+    dx, dc = A + (5 << 29), A + (6 << 29)
+    grads = ctypes.byref(_lib.BcaGrads(dx, dc))
+    assert lib.bca_backward_keep(A, B, G, grads, d, d, p, t, F32, None) == _lib.RDFFT_EDEVICE
+    assert lib.bca_backward_keep(A, B, A, grads, d, d, p, t, F32, None) == _lib.RDFFT_EDEVICE  # gy is x
+    assert lib.bca_backward_keep(A, B, dx, grads, d, d, p, t, F32, None) == EINVAL  # dx is gy
+    assert lib.bca_backward_keep(A, B, dx + 64, grads, d, d, p, t, F32, None) == EINVAL
+    assert lib.bca_backward_keep(dx, B, G, grads, d, d, p, t, F32, None) == EINVAL  # dx is x
+    assert lib.bca_backward_keep(A, B, G, None, d, d, p, t, F32, None) == EINVAL
+    assert lib.bca_backward_keep(A, B, G, grads, 16384, 16384, 16384, t, F32, None) == EUNSUP
+
+
 def test_bca_backward_needs_grads(lib):
     assert lib.bca_backward(A, B, G, None, 256, 256, 64, 8, F32, None) == EINVAL
 

@@ -97,6 +97,41 @@ def test_clobber_grad_reuses_the_upstream_gradient():
         assert_close(lay.c.grad.double().cpu().numpy().reshape(-1, p), dc_ref.reshape(-1, p), "f32", f"dc {name}")
 
 
+@pytest.mark.parametrize("d_in,d_out,p,tokens", [(768, 768, 256, 2100), (2048, 2048, 1024, 1100), (2048, 512, 128, 2100),
+                                                 (64, 64, 16, 5), (512, 256, 32, 9)])
+def test_backward_leaves_the_gradient_bits(d_in, d_out, p, tokens):
+    """Token counts at which the library would stage its dC sums in a gradient it may overwrite."""
+    layer = BlockCirculantLinear(d_in, d_out, p, dtype=torch.bfloat16)
+    x = torch.randn(tokens, d_in, device="cuda").bfloat16().requires_grad_(True)
+    g = torch.randn(tokens, d_out, device="cuda").bfloat16()
+    kept = g.clone()
+    layer(x).backward(g)
+    dx, dc = x.grad.clone(), layer.c.grad.clone()
+    assert torch.equal(g, kept)
+    other = BlockCirculantLinear(d_in, d_out, p, dtype=torch.bfloat16, clobber_grad=True)
+    other.c.data.copy_(layer.c.data)
+    x.grad = None
+    other(x).backward(g)
+    assert torch.equal(x.grad, dx)
+    # dc: float32 sums in another order
+    torch.testing.assert_close(other.c.grad, dc, rtol=0, atol=1e-5 * dc.square().mean().sqrt().item() * tokens**0.5)
+
+
+def test_backward_takes_any_gradient():
+    """Gradients that the library itself refuses: a view that starts off its 16-byte grid, x itself, an
+    expanded row."""
+    d, p = 256, 64
+    layer = BlockCirculantLinear(d, d, p, dtype=torch.float32)
+    x = torch.randn(6, d, device="cuda").requires_grad_(True)
+    room = torch.randn(6 * d + 1, device="cuda")
+    for g in (room[1:].view(6, d), x.detach(), room[:d].expand(6, d)):
+        want = torch.autograd.grad(layer(x), (x, layer.c), g.clone().contiguous())
+        kept = g.clone()
+        got = torch.autograd.grad(layer(x), (x, layer.c), g)
+        assert torch.equal(g, kept) and torch.equal(got[0], want[0])
+        torch.testing.assert_close(got[1], want[1], rtol=1e-5, atol=1e-4)
+
+
 def test_training_step_reduces_loss():
     # a few SGD steps toward a fixed circulant target: the gradient points downhill
     torch.manual_seed(0)
