@@ -280,11 +280,10 @@ struct BcaSqFwd {
 };
 constexpr int kFwdSqWG = 512;
 
-template <int LOGN, class St, int QB, int WG = kFwdSqWG>
-__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(BcaSqFwd<LOGN, QB, WG>::MIN_WAVES)))
-bca_forward_sq_kernel(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c,
-                                                                     ElemOf<St>* y, int64_t tokens, int tt_per_tile,
-                                                                     int64_t ntiles, const float2* __restrict__ tw) {
+template <int LOGN, class St, int QB, int WG>
+__device__ __forceinline__ void forward_sq(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c, ElemOf<St>* y,
+                                           int64_t tokens, int tt_per_tile, int64_t ntiles,
+                                           const float2* __restrict__ tw) {
   using B = BcaPlan<LOGN>;
   using S = BcaSqFwd<LOGN, QB, WG>;
   using In = typename St::In;
@@ -379,6 +378,13 @@ bca_forward_sq_kernel(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c,
   }
 }
 
+template <int LOGN, class St, int QB, int WG = kFwdSqWG>
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(BcaSqFwd<LOGN, QB, WG>::MIN_WAVES)))
+bca_forward_sq_kernel(const ElemOf<St>* x, const ElemOf<St>* __restrict__ c, ElemOf<St>* y, int64_t tokens,
+                      int tt_per_tile, int64_t ntiles, const float2* __restrict__ tw) {
+  forward_sq<LOGN, St, QB, WG>(x, c, y, tokens, tt_per_tile, ntiles, tw);
+}
+
 // Backward for square layers (q == kb == QB) with few blocks: every thread owns a fixed
 // set of (bin, input block) slots for the whole kernel, keeps C_ij[k] and its dC_ij[k]
 // partial sums for them in registers, and so touches LDS only to read X_j[k], G_i[k]
@@ -413,12 +419,11 @@ constexpr int sq_bwd_wg() {
   return S::BT * S::NSL > kSqMaxSlots && S2::BT * S2::NSL <= kSqMaxSlots && BcaPlan<LOGN>::N <= 1024 ? 1024 : wg;
 }
 
-template <int LOGN, class St, int QB, int WG = sq_bwd_wg<LOGN, QB>()>
-__global__ void __launch_bounds__(WG) bca_backward_sq_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __restrict__ c,
-                                                                      const ElemOf<St>* gy, ElemOf<St>* dx, float* __restrict__ dc,
-                                                                      int64_t tokens, int tt_per_tile, int64_t ntiles,
-                                                                      float2* stage, int64_t tile_f2, int chunk,
-                                                                      const float2* __restrict__ tw) {
+template <int LOGN, class St, int QB, int WG>
+__device__ __forceinline__ void backward_sq(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __restrict__ c,
+                                            const ElemOf<St>* gy, ElemOf<St>* dx, float* __restrict__ dc,
+                                            int64_t tokens, int tt_per_tile, int64_t ntiles, float2* stage,
+                                            int64_t tile_f2, int chunk, const float2* __restrict__ tw) {
   using B = BcaPlan<LOGN>;
   using S = BcaSq<LOGN, QB, WG>;
   using In = typename St::In;
@@ -559,6 +564,14 @@ __global__ void __launch_bounds__(WG) bca_backward_sq_kernel(const ElemOf<St>* _
     unsafeAtomicAdd(dc + 2 * (int64_t)e, v.x);
     unsafeAtomicAdd(dc + 2 * (int64_t)e + 1, v.y);
   }
+}
+
+template <int LOGN, class St, int QB, int WG = sq_bwd_wg<LOGN, QB>()>
+__global__ void __launch_bounds__(WG)
+bca_backward_sq_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __restrict__ c, const ElemOf<St>* gy,
+                       ElemOf<St>* dx, float* __restrict__ dc, int64_t tokens, int tt_per_tile, int64_t ntiles,
+                       float2* stage, int64_t tile_f2, int chunk, const float2* __restrict__ tw) {
+  backward_sq<LOGN, St, QB, WG>(x, c, gy, dx, dc, tokens, tt_per_tile, ntiles, stage, tile_f2, chunk, tw);
 }
 
 // The fill of dc, and the second stage of the two-stage dC sum (bca_kernels.hip): the
@@ -870,6 +883,35 @@ struct WavePtrs {
   float* dc[MAXB];
 };
 
+// Three 3 x 3 blocks of 256 fill six of a wave's eight row slots, and every transform round of
+// the wave kernels runs the other two idle.  With tokens enough for several tiles per workgroup
+// the square-layer kernels in workgroups of two waves do better: five tokens fill 15 of 16
+// slots, the two waves wait only for each other, and each thread keeps its bin's C (and dC).
+// One layer of 98304 tokens, bf16: forward 137 -> 112 us, backward 247 -> 217 us; of 32768: 46 -> 40
+// and 86 -> 83 us; of 4096 (less than a tile each): 8.4 -> 8.8 us.  1, 2 and 4 blocks fill the wave
+// kernels' rounds, which are then the faster ones (backward of 1 x 1: 67 us against 106).
+constexpr int kPairWG = 128, kPairTokens = 5;
+constexpr int kPairFwdPerCu = 8, kPairBwdPerCu = 4;  // workgroups per CU
+constexpr int64_t kPairFwdMinTokens = 24576, kPairBwdMinTokens = 49152;  // of all layers of a launch
+template <int LOGN, int QB>
+constexpr bool pair_layer() { return LOGN == 7 && QB == 3; }
+
+template <int LOGN, class St, int QB, int MAXB>
+__global__ void __launch_bounds__(kPairWG) __attribute__((amdgpu_waves_per_eu(4)))
+bca_forward_pair_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int tt_per_tile, int64_t ntiles,
+                        const float2* __restrict__ tw) {
+  const int bi = MAXB == 1 ? 0 : (int)blockIdx.y;
+  forward_sq<LOGN, St, QB, kPairWG>(ptrs.x[bi], ptrs.c[bi], ptrs.y[bi], tokens, tt_per_tile, ntiles, tw);
+}
+template <int LOGN, class St, int QB, int MAXB>
+__global__ void __launch_bounds__(kPairWG)
+bca_backward_pair_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int tt_per_tile, int64_t ntiles, int64_t tile_f2, int chunk,
+                         const float2* __restrict__ tw) {
+  const int bi = MAXB == 1 ? 0 : (int)blockIdx.y;
+  backward_sq<LOGN, St, QB, kPairWG>(ptrs.x[bi], ptrs.c[bi], ptrs.y[bi], ptrs.dx[bi], ptrs.dc[bi], tokens, tt_per_tile,
+                                     ntiles, reinterpret_cast<float2*>(ptrs.y[bi]), tile_f2, chunk, tw);
+}
+
 // Forward: per group, X_j = rdFFT(x_j) into the wave's LDS regions, Y_i = sum_j C_ij X_j
 // per bin written over X_i (a lane reads every X_j[k] of its bin before it writes), then
 // y_i = irdFFT(Y_i).  y may be x: a wave reads its group's x rows before it writes the
@@ -1103,6 +1145,17 @@ constexpr size_t wave_lds_bytes(bool backward) {
 template <int LOGN, class St, int QB, int MAXB>
 static hipError_t fwd_wave_launch(const WavePtrs<St, MAXB>& ptrs, int count, int64_t tokens, const float2* tw,
                                   hipStream_t stream, int num_cu) {
+  if constexpr (pair_layer<LOGN, QB>()) {
+    if (tokens * count >= kPairFwdMinTokens) {
+      constexpr size_t lds = (size_t)(kPairTokens * QB + 1) * BcaPlan<LOGN>::REGION * sizeof(float2);
+      static_assert(lds * kPairFwdPerCu <= (size_t)kLdsLimit, "tokens too many for LDS");
+      const int64_t tiles = (tokens + kPairTokens - 1) / kPairTokens;
+      const int64_t grid = std::min<int64_t>(tiles, ((int64_t)num_cu * kPairFwdPerCu + count - 1) / count);
+      hipLaunchKernelGGL((bca_forward_pair_kernel<LOGN, St, QB, MAXB>), dim3((unsigned)grid, (unsigned)count),
+                         dim3(kPairWG), lds, stream, ptrs, tokens, kPairTokens, tiles, tw);
+      return hipGetLastError();
+    }
+  }
   constexpr int TW = wave_tokens<LOGN, QB>(), NW = kWaveFwdNW;
   constexpr size_t lds = wave_lds_bytes<LOGN, QB>(false);
   static_assert(lds <= (size_t)kLdsLimit, "wave groups too large for LDS");
@@ -1135,6 +1188,21 @@ struct FinishPtrs {
 hipError_t launch_dc_finish_batched(const FinishPtrs<kMaxBatch>& p, int count, int rows_ij, int logn, int chunk,
                                     int groups, int64_t tile_f2, const float2* tw, hipStream_t stream);
 
+// the second stage of every layer of a launch, its partial sums in its own gy rows
+template <class St, int MAXB>
+static hipError_t finish_layers(const WavePtrs<St, MAXB>& ptrs, int count, int rows_ij, int logn, int chunk, int groups,
+                                int64_t tile_f2, const float2* tw, hipStream_t stream) {
+  if (count == 1)
+    return launch_dc_finish(reinterpret_cast<const float2*>(ptrs.y[0]), ptrs.dc[0], rows_ij, logn, chunk, groups, tile_f2,
+                            tw, stream);
+  FinishPtrs<kMaxBatch> f{};
+  for (int b = 0; b < count; ++b) {
+    f.stage[b] = reinterpret_cast<const float2*>(ptrs.y[b]);
+    f.dc[b] = ptrs.dc[b];
+  }
+  return launch_dc_finish_batched(f, count, rows_ij, logn, chunk, groups, tile_f2, tw, stream);
+}
+
 template <int LOGN, class St, int QB, int MAXB>
 static hipError_t bwd_wave_launch(const WavePtrs<St, MAXB>& ptrs, int count, bool apart, int64_t tokens,
                                   const float2* tw, hipStream_t stream, int num_cu) {
@@ -1147,13 +1215,34 @@ static hipError_t bwd_wave_launch(const WavePtrs<St, MAXB>& ptrs, int count, boo
   if (attr != hipSuccess) return attr;
   const int64_t groups = (tokens + TW - 1) / TW;
   // one workgroup per CU in all: fewer workgroups, fewer dC partial sums to add
-  const int64_t grid = std::max<int64_t>(1, std::min<int64_t>((groups + NW - 1) / NW, num_cu / count));
+  int64_t grid = std::max<int64_t>(1, std::min<int64_t>((groups + NW - 1) / NW, num_cu / count));
+  // a batch is staged whenever one workgroup's groups are whole: the last, partial one's go to the
+  // others, since the layers one by one (three launches each) cost more than its absence (17
+  // layers of one 128-block, 796 tokens, forward + backward: 214 us one by one, 132 us staged)
+  if (count > 1 && apart) grid = std::min<int64_t>(grid, std::max<int64_t>(1, tokens / (NW * TW)));
   // Two-stage dC sum when dx has its own buffer and gy may be written (apart): workgroup b's first groups are the
   // tokens [b*NW*TW, (b+1)*NW*TW), whose gy rows only it reads; once all its waves are
   // done it writes its partial sums there (QKN float2 must fit those rows, all of them
   // valid tokens)
   const int64_t region_f2 = (int64_t)NW * TW * QB * W::N * (int64_t)sizeof(ElemOf<St>) / (int64_t)sizeof(float2);
   const bool staged = apart && region_f2 >= QKN && grid * NW * TW <= tokens;
+  if constexpr (pair_layer<LOGN, QB>()) {
+    const int64_t tiles = (tokens + kPairTokens - 1) / kPairTokens;
+    const int64_t tile_f2 = (int64_t)kPairTokens * QB * W::N * (int64_t)sizeof(ElemOf<St>) / (int64_t)sizeof(float2);
+    const int chunk = (int)std::min<int64_t>(QKN, tile_f2);
+    const int64_t chunks = (QKN + chunk - 1) / chunk;
+    const int64_t pgrid = std::min<int64_t>(tiles, std::max<int64_t>(1, (int64_t)num_cu * kPairBwdPerCu / count));
+    if (apart && tokens * count >= kPairBwdMinTokens && chunks * pgrid <= tokens / kPairTokens) {
+      constexpr size_t plds = (size_t)(kPairTokens * 2 * QB + 1) * BcaPlan<LOGN>::REGION * sizeof(float2);
+      static_assert(plds * kPairBwdPerCu <= (size_t)kLdsLimit, "tokens too many for LDS");
+      static_assert(plds >= (size_t)QKN * sizeof(float2), "the partial sums pass through the spectra's LDS");
+      hipLaunchKernelGGL((bca_backward_pair_kernel<LOGN, St, QB, MAXB>), dim3((unsigned)pgrid, (unsigned)count),
+                         dim3(kPairWG), plds, stream, ptrs, tokens, kPairTokens, tiles, tile_f2, chunk, tw);
+      const hipError_t ep = hipGetLastError();
+      if (ep != hipSuccess) return ep;
+      return finish_layers<St, MAXB>(ptrs, count, QB * QB, LOGN, chunk, (int)pgrid, tile_f2, tw, stream);
+    }
+  }
   if (!staged && count > 1) {
     // too few tokens to stage a batch's partial sums: the layers one by one
     for (int b = 0; b < count; ++b) {
@@ -1171,17 +1260,7 @@ static hipError_t bwd_wave_launch(const WavePtrs<St, MAXB>& ptrs, int count, boo
                      dim3(64 * NW), lds, stream, ptrs, tokens, groups, staged ? 1 : 0, region_f2, tw);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (staged) {
-    if (count == 1)
-      return launch_dc_finish(reinterpret_cast<const float2*>(ptrs.y[0]), ptrs.dc[0], QB * QB, LOGN, QKN, (int)grid,
-                              region_f2, tw, stream);
-    FinishPtrs<kMaxBatch> f{};
-    for (int b = 0; b < count; ++b) {
-      f.stage[b] = reinterpret_cast<const float2*>(ptrs.y[b]);
-      f.dc[b] = ptrs.dc[b];
-    }
-    return launch_dc_finish_batched(f, count, QB * QB, LOGN, QKN, (int)grid, region_f2, tw, stream);
-  }
+  if (staged) return finish_layers<St, MAXB>(ptrs, count, QB * QB, LOGN, QKN, (int)grid, region_f2, tw, stream);
   return launch_rdfft_rows(ptrs.dc[0], (int64_t)QB * QB, LOGN, kStorageF32, true, tw, stream, num_cu);
 }
 

@@ -78,7 +78,9 @@ def _init():
 
 # (count, tokens, d, p, dtype): side by side in the wave kernels
 FUSED = [(24, 256, 768, 256, "bf16"), (40, 64, 256, 128, "bf16"), (5, 256, 1024, 512, "f16"),
-         (3, 100, 512, 128, "f32")]  # the last: a forward side by side, a backward too short to stage
+         (3, 100, 512, 128, "f32"),  # a forward side by side, a backward too short to stage
+         (17, 203, 128, 128, "bf16"),  # staged by fewer workgroups than would fit, with a ragged end
+         (16, 3077, 768, 256, "bf16")]  # tokens enough for the two-wave workgroups, a ragged last tile
 
 
 @pytest.mark.parametrize("shape", FUSED, ids=[f"n{s[0]}_T{s[1]}_{s[2]}_p{s[3]}_{s[4]}" for s in FUSED])
