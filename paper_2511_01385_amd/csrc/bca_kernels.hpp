@@ -56,6 +56,24 @@ using ElemOf = typename St::Elem;
 
 extern __shared__ float2 bca_lds[];
 
+// Adds `count` floats of LDS (and those of COPIES - 1 further copies, `count` floats apart) into
+// dst by float32 atomics.  Consecutive lanes take consecutive floats: an instruction then touches two
+// cache lines, where the pairs' x and y parts one after the other touched four each, and the lines are
+// what the atomics wait for (4096-wide bf16 layer with dx over gy: 74 us by pairs).  Workgroup b
+// starts 128*b floats in, so that the workgroups, which all finish together, do not queue on the
+// same addresses.
+template <int WG, int COPIES>
+__device__ __forceinline__ void atomic_add_rotated(float* __restrict__ dst, const float* part, int count) {
+  const int shift = (int)(((unsigned)blockIdx.x * 128u) % (unsigned)count);
+  for (int f0 = threadIdx.x; f0 < count; f0 += WG) {
+    int f = f0 + shift;
+    if (f >= count) f -= count;
+    float v = part[f];
+    static_for<COPIES - 1>([&](auto pc) { v += part[(size_t)(decltype(pc)::value + 1) * count + f]; });
+    unsafeAtomicAdd(dst + f, v);
+  }
+}
+
 // x: [T][kb*N] pairs, c: [q][kb][N] pairs, y: [T][q*N] pairs (all in the storage type St).
 // y may be x itself (kb == q): a workgroup reads a tile's x rows before it writes the
 // tile's y rows, and no other workgroup touches them, so x is not declared restrict.
@@ -243,19 +261,17 @@ __global__ void __launch_bounds__(WG) bca_backward_kernel(const ElemOf<St>* __re
 
   if (!do_dc) return;
   __syncthreads();
-  // fold this workgroup's partial sums into dc; workgroup b starts 64*b slots in, so
-  // that the workgroups, which all finish together, do not queue on the same addresses
-  const int shift = (int)(((unsigned)blockIdx.x * 64u) % (unsigned)qkn);
-  for (int e0 = tid; e0 < qkn; e0 += WG) {
-    int e = e0 + shift;
-    if (e >= qkn) e -= qkn;
-    const float2 v = acc[e];
-    const int k = e & (N - 1);
-    const int ij = e / N;
+  // fold this workgroup's partial sums into dc, float by float and from a rotated start (as
+  // atomic_add_rotated; here a launch's blocks may be a range of dc's)
+  const float* accf = reinterpret_cast<const float*>(acc);
+  const int count = 2 * qkn, shift = (int)(((unsigned)blockIdx.x * 128u) % (unsigned)count);
+  for (int f0 = tid; f0 < count; f0 += WG) {
+    int f = f0 + shift;
+    if (f >= count) f -= count;
+    const int k = f & (2 * N - 1);
+    const int ij = f / (2 * N);
     const int ii = ij / jb, jj = ij - ii * jb;
-    const int64_t d = ((int64_t)(i0 + ii) * kb + (j0 + jj)) * N + k;
-    unsafeAtomicAdd(dc + 2 * d, v.x);
-    unsafeAtomicAdd(dc + 2 * d + 1, v.y);
+    unsafeAtomicAdd(dc + ((int64_t)(i0 + ii) * kb + (j0 + jj)) * 2 * N + k, accf[f]);
   }
 }
 
@@ -529,9 +545,7 @@ __device__ __forceinline__ void backward_sq(const ElemOf<St>* __restrict__ x, co
   }
 
   // Fold the partial sums into dc (slot e = (i*QB + j)*N + k, float2).  They are staged
-  // in LDS as [TS][QB*QB*N], the TS token phases summed, and the atomics issued from a
-  // rotated start: workgroup b begins 64*b slots in, so that the workgroups, which all
-  // finish together, do not queue on the same addresses.
+  // in LDS as [TS][QB*QB*N] and the TS token phases summed.
   constexpr int QKN = QB * QB * N;
   float2* const part = bca_lds;
   static_for<BT>([&](auto wc) {
@@ -555,15 +569,7 @@ __device__ __forceinline__ void backward_sq(const ElemOf<St>* __restrict__ x, co
     }
     return;
   }
-  const int shift = (int)(((unsigned)blockIdx.x * 64u) % (unsigned)QKN);
-  for (int e0 = tid; e0 < QKN; e0 += WG) {
-    int e = e0 + shift;
-    if (e >= QKN) e -= QKN;
-    float2 v = part[e];
-    static_for<TS - 1>([&](auto pc) { v = c_add(v, part[(size_t)(decltype(pc)::value + 1) * QKN + e]); });
-    unsafeAtomicAdd(dc + 2 * (int64_t)e, v.x);
-    unsafeAtomicAdd(dc + 2 * (int64_t)e + 1, v.y);
-  }
+  atomic_add_rotated<WG, TS>(dc, reinterpret_cast<const float*>(part), 2 * QKN);
 }
 
 template <int LOGN, class St, int QB, int WG = sq_bwd_wg<LOGN, QB>()>
@@ -1116,15 +1122,7 @@ bca_backward_wave_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int64_t ngroup
     }
     return;
   }
-  const int shift = (int)(((unsigned)blockIdx.x * 64u) % (unsigned)QKN);
-  for (int e0 = threadIdx.x; e0 < QKN; e0 += (64 * NW)) {
-    int e = e0 + shift;
-    if (e >= QKN) e -= QKN;
-    float2 v = part[e];
-    static_for<NW - 1>([&](auto wc) { v = c_add(v, part[(size_t)(decltype(wc)::value + 1) * QKN + e]); });
-    unsafeAtomicAdd(dc + 2 * (int64_t)e, v.x);
-    unsafeAtomicAdd(dc + 2 * (int64_t)e + 1, v.y);
-  }
+  atomic_add_rotated<64 * NW, NW>(dc, reinterpret_cast<const float*>(part), 2 * QKN);
 }
 
 // LDS of one workgroup of the wave kernels
