@@ -733,20 +733,25 @@ static hipError_t bwd_impl(const BcaArgs& a, const float2* tw, hipStream_t strea
 // Square layers with few blocks: register-resident C and dC (bca_backward_sq_kernel)
 constexpr int kSqMaxBlocks = 4;  // q == kb <= 4
 
-// Tokens per tile of the square-layer kernels: the largest TT (at most 64 and the token
-// count) whose TT*rpt spectra, plus a spare region when TT*QB transforms leave some of
-// the ng row groups idle, fit in `budget` bytes.  0 when one token does not fit.
-// Tokens per tile of the square-layer kernels: the most whose regions fit `budget`, at most
-// 64, and (spread > 0) at most tokens / spread, so that a short batch still reaches `spread`
-// workgroups.  The forward spreads over the CUs (the 256-wide layer's 128 tokens: 2 tiles of 64,
-// 7.5 us; 128 tiles of 1, 4.0 us); the backward does not, since every workgroup adds a dC
-// partial sum (1024-wide, 512 tokens: 31 us as is, 40 us spread).
+// Tokens per tile of the square-layer kernels: the largest TT whose TT*rpt spectra, plus a spare
+// region when TT*QB transforms leave some of the ng row groups idle, fit in `budget` bytes; at most
+// 64, the token count, and tokens / spread, so that a short batch still reaches `spread`
+// workgroups.  A TT that could fill whole rounds of row groups does: one block of 1024 took 17
+// tokens for 16 groups, two rounds of each transform (backward of 4096 tokens 26.9 us; 23.6 with
+// 16 tokens).  0 when one token does not fit.
+// The forward spreads over all CUs (the 256-wide layer's 128 tokens: 2 tiles of 64, 7.5 us; 128
+// tiles of 1, 4.0 us).  The backward spreads over 64 workgroups: each adds a dC partial sum, on the
+// same addresses (256-wide, p = 64, 128 tokens: 2 workgroups 15.7 us, 64 workgroups 11.1 us, 128
+// workgroups 12.8 us; p = 32, 512 tokens: 8, 64 and 256 workgroups 11.8, 10.0 and 13.8 us).
+constexpr int kSqBwdSpread = 64;
 static int sq_tokens_per_tile(int logn, int rpt, int qb, int ng, int64_t tokens, int64_t budget, bool* spare,
                               int spread = 0) {
   const int64_t rb = region_bytes(logn);
   int64_t top = std::min<int64_t>(64, std::max<int64_t>(tokens, 1));
   if (spread > 0) top = std::min<int64_t>(top, std::max<int64_t>(1, (tokens + spread - 1) / spread));
+  const int whole = ng / gcd_int(ng, qb);  // tokens whose transforms fill whole rounds of the row groups
   for (int tt = (int)top; tt >= 1; --tt) {
+    if (tt > whole && tt % whole != 0) continue;
     const bool sp = (tt * qb) % ng != 0;
     if ((tt * rpt + (sp ? 1 : 0)) * rb <= budget) {
       *spare = sp;
@@ -796,7 +801,8 @@ static hipError_t bwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t st
   constexpr int WG = sq_bwd_wg<LOGN, QB>();
   using S = BcaSq<LOGN, QB, WG>;
   bool spare = false;
-  const int TT = sq_tokens_per_tile(LOGN, 2 * QB, QB, WG / BcaPlan<LOGN>::TPR, a.tokens, kLdsLimit, &spare);
+  const int TT = sq_tokens_per_tile(LOGN, 2 * QB, QB, WG / BcaPlan<LOGN>::TPR, a.tokens, kLdsLimit, &spare,
+                                    kSqBwdSpread);
   if (TT == 0) return hipErrorInvalidValue;
   const size_t spectra = (size_t)(TT * 2 * QB + (spare ? 1 : 0)) * region_bytes(LOGN);
   const size_t part = (size_t)S::TS * QB * QB * S::N * sizeof(float2);  // [TS][QB*QB*N]
