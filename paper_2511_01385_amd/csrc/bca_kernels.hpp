@@ -432,6 +432,11 @@ constexpr int sq_bwd_wg() {
   if constexpr (wg == 1024 || BcaPlan<LOGN>::TPR < 64) return wg;
   using S = BcaSq<LOGN, QB, wg>;
   using S2 = BcaSq<LOGN, QB, 1024>;
+  // One block of 8192: LDS holds one workgroup's two tokens whatever its size, and what bounds the
+  // kernel is VALU issue (69 us of it for 4096 tokens) with too few waves to reach it.  Sixteen
+  // waves instead of eight run a tile's four forward transforms in one round: forward + backward
+  // 167 -> 159 us (bf16, 4096 tokens), in 128 registers without spills.
+  if constexpr (BcaPlan<LOGN>::N == 4096 && QB == 1) return 1024;
   return S::BT * S::NSL > kSqMaxSlots && S2::BT * S2::NSL <= kSqMaxSlots && BcaPlan<LOGN>::N <= 1024 ? 1024 : wg;
 }
 
@@ -533,6 +538,14 @@ __device__ __forceinline__ void backward_sq(const ElemOf<St>* __restrict__ x, co
 
     // Phase C: dx_j = irdFFT(dX_j)
     for (int s0 = 0; s0 < nx; s0 += NG) {
+      if constexpr (TPR > 64) {
+        // a row group without a row (uniform over its waves) only keeps the others' barriers: it needs
+        // no region and leaves the VALUs to them
+        if (s0 + __builtin_amdgcn_readfirstlane(grp) >= nx) {
+          for (int b = 0; b < row_inverse_syncs<LOGN, true>(); ++b) __syncthreads();
+          continue;
+        }
+      }
       const int s = s0 + grp;
       const bool valid = s < nx;
       const int tt = valid ? s / QB : 0, j = valid ? s - tt * QB : 0;
@@ -734,7 +747,7 @@ static hipError_t bwd_impl(const BcaArgs& a, const float2* tw, hipStream_t strea
 constexpr int kSqMaxBlocks = 4;  // q == kb <= 4
 
 // Tokens per tile of the square-layer kernels: the largest TT whose TT*rpt spectra, plus a spare
-// region when TT*QB transforms leave some of the ng row groups idle, fit in `budget` bytes; at most
+// region when TT*spare_rows transforms leave some of the ng row groups idle, fit in `budget` bytes; at most
 // 64, the token count, and tokens / spread, so that a short batch still reaches `spread`
 // workgroups.  A TT that could fill whole rounds of row groups does: one block of 1024 took 17
 // tokens for 16 groups, two rounds of each transform (backward of 4096 tokens 26.9 us; 23.6 with
@@ -744,15 +757,15 @@ constexpr int kSqMaxBlocks = 4;  // q == kb <= 4
 // same addresses (256-wide, p = 64, 128 tokens: 2 workgroups 15.7 us, 64 workgroups 11.1 us, 128
 // workgroups 12.8 us; p = 32, 512 tokens: 8, 64 and 256 workgroups 11.8, 10.0 and 13.8 us).
 constexpr int kSqBwdSpread = 64;
-static int sq_tokens_per_tile(int logn, int rpt, int qb, int ng, int64_t tokens, int64_t budget, bool* spare,
-                              int spread = 0) {
+static int sq_tokens_per_tile(int logn, int rpt, int qb, int spare_rows, int ng, int64_t tokens, int64_t budget,
+                              bool* spare, int spread = 0) {
   const int64_t rb = region_bytes(logn);
   int64_t top = std::min<int64_t>(64, std::max<int64_t>(tokens, 1));
   if (spread > 0) top = std::min<int64_t>(top, std::max<int64_t>(1, (tokens + spread - 1) / spread));
   const int whole = ng / gcd_int(ng, qb);  // tokens whose transforms fill whole rounds of the row groups
   for (int tt = (int)top; tt >= 1; --tt) {
     if (tt > whole && tt % whole != 0) continue;
-    const bool sp = (tt * qb) % ng != 0;
+    const bool sp = (tt * spare_rows) % ng != 0;
     if ((tt * rpt + (sp ? 1 : 0)) * rb <= budget) {
       *spare = sp;
       return tt;
@@ -775,8 +788,8 @@ static hipError_t fwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t st
   constexpr int ng = WG / BcaPlan<LOGN>::TPR;
   // two workgroups per CU, or one when a token's spectra need more than half the LDS
   bool spare = false;
-  int TT = sq_tokens_per_tile(LOGN, rpt, QB, ng, a.tokens, kLdsLimit / 2, &spare, num_cu);
-  if (TT == 0) TT = sq_tokens_per_tile(LOGN, rpt, QB, ng, a.tokens, kLdsLimit, &spare, num_cu);
+  int TT = sq_tokens_per_tile(LOGN, rpt, QB, QB, ng, a.tokens, kLdsLimit / 2, &spare, num_cu);
+  if (TT == 0) TT = sq_tokens_per_tile(LOGN, rpt, QB, QB, ng, a.tokens, kLdsLimit, &spare, num_cu);
   if (TT == 0) return hipErrorInvalidValue;
   const size_t lds = (size_t)(TT * rpt + (spare ? 1 : 0)) * region_bytes(LOGN);
   static const hipError_t attr = set_lds_limit(bca_forward_sq_kernel<LOGN, St, QB>);
@@ -801,8 +814,9 @@ static hipError_t bwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t st
   constexpr int WG = sq_bwd_wg<LOGN, QB>();
   using S = BcaSq<LOGN, QB, WG>;
   bool spare = false;
-  const int TT = sq_tokens_per_tile(LOGN, 2 * QB, QB, WG / BcaPlan<LOGN>::TPR, a.tokens, kLdsLimit, &spare,
-                                    kSqBwdSpread);
+  // (rows beyond a wave: groups without a row of the inverse round take no region)
+  const int TT = sq_tokens_per_tile(LOGN, 2 * QB, QB, BcaPlan<LOGN>::TPR > 64 ? 2 * QB : QB, WG / BcaPlan<LOGN>::TPR,
+                                    a.tokens, kLdsLimit, &spare, kSqBwdSpread);
   if (TT == 0) return hipErrorInvalidValue;
   const size_t spectra = (size_t)(TT * 2 * QB + (spare ? 1 : 0)) * region_bytes(LOGN);
   const size_t part = (size_t)S::TS * QB * QB * S::N * sizeof(float2);  // [TS][QB*QB*N]

@@ -831,6 +831,13 @@ __device__ __forceinline__ void load_inverse(int t, const Src& src, typename Src
   }
 }
 
+// Row barriers of row_inverse_loaded (LOGN > 0, TPR > 1): around the mirror exchange and two per
+// round of every Stockham exchange.  Waves without a row wait this many times instead.
+template <int LOGN, bool SRC_IN_LDS, int CH = kChunks[LOGN]>
+constexpr int row_inverse_syncs() {
+  return (SRC_IN_LDS ? 1 : 0) + 2 + 2 * CH * (RowPlan<LOGN>::NP - 1);
+}
+
 template <int LOGN, bool SRC_IN_LDS, class Src, class Dst, int CH = kChunks[LOGN]>
 __device__ __forceinline__ void row_inverse_loaded(int t, bool active, const typename Src::raw_t* raw,
                                                    const Dst& dst, float2* lds, const float2* __restrict__ tw) {
