@@ -223,8 +223,6 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t tok0 = tile * TT;
     const int nvalid = (int)(tokens - tok0 < TT ? tokens - tok0 : TT);
-    const float2* twg = tw;  // opaque per tile: keeps twiddle reads out of the loop's live registers
-    asm volatile("" : "+s"(twg));
 
     const int per = kb + q, ns = TT * per;
 #pragma unroll 1
@@ -237,7 +235,7 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
       float2* reg = valid ? xs + tt * TS + m * REG : dummy;
       const int64_t tok = act ? tok0 + tt : 0;
       const ElemOf<St>* srcp = m < kb ? x + (tok * kb + m) * (int64_t)N : gy + (tok * q + (m - kb)) * (int64_t)N;
-      row_forward<LOGN, true>(t, act, In{srcp}, LdsSpectrum{reg}, reg, twg);
+      row_forward<LOGN, true>(t, act, In{srcp}, LdsSpectrum{reg}, reg, reread(tw));
     }
     __syncthreads();
 
@@ -350,7 +348,7 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
       const bool act = valid && tt < nvalid;
       float2* reg = valid ? xs + tt * TS + j * REG : dummy;
       const Out dst{dx + ((act ? tok0 + tt : 0) * kb + j) * (int64_t)N};
-      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, twg);
+      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, reread(tw));
     }
     __syncthreads();
   }

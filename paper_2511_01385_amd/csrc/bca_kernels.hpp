@@ -435,7 +435,7 @@ constexpr int sq_bwd_wg() {
   // One block of 8192: LDS holds one workgroup's two tokens whatever its size, and what bounds the
   // kernel is VALU issue (69 us of it for 4096 tokens) with too few waves to reach it.  Sixteen
   // waves instead of eight run a tile's four forward transforms in one round: forward + backward
-  // 167 -> 159 us (bf16, 4096 tokens), in 128 registers without spills.
+  // 167 -> 159 us (bf16, 4096 tokens), in 127 registers without spills.
   if constexpr (BcaPlan<LOGN>::N == 4096 && QB == 1) return 1024;
   return S::BT * S::NSL > kSqMaxSlots && S2::BT * S2::NSL <= kSqMaxSlots && BcaPlan<LOGN>::N <= 1024 ? 1024 : wg;
 }
@@ -450,6 +450,7 @@ __device__ __forceinline__ void backward_sq(const ElemOf<St>* __restrict__ x, co
   using In = typename St::In;
   using Out = typename St::Out;
   constexpr int N = B::N, TPR = B::TPR, NG = WG / TPR, REG = B::REGION;
+  constexpr bool REREAD = WG == 1024 && B::P::E == 16;  // 128 registers: twiddles read anew per transform
   constexpr int TB = S::TB, BT = S::BT, TJ = S::TJ, TS = S::TS, JPT = S::JPT, NSL = S::NSL;
   const int tid = threadIdx.x;
   const int grp = tid / TPR, t = tid - grp * TPR;
@@ -488,8 +489,6 @@ __device__ __forceinline__ void backward_sq(const ElemOf<St>* __restrict__ x, co
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t tok0 = tile * TT;
     const int nvalid = (int)(tokens - tok0 < TT ? tokens - tok0 : TT);
-    const float2* twg = tw;
-    if constexpr (WG == 1024 && B::P::E == 16) asm volatile("" : "+s"(twg));  // twiddles read anew per tile
 
     // Phase A: X_j = rdFFT(x_j), G_i = rdFFT(g_i)
     const int nx = TT * QB, ns = 2 * TT * QB;
@@ -502,7 +501,7 @@ __device__ __forceinline__ void backward_sq(const ElemOf<St>* __restrict__ x, co
       const bool act = valid && tt < nvalid;
       const ElemOf<St>* base = s < nx ? x : gy;
       const ElemOf<St>* srcp = base + ((act ? tok0 + tt : 0) * QB + j) * (int64_t)N;
-      row_forward<LOGN, true>(t, act, In{srcp}, LdsSpectrum{reg}, reg, twg);
+      row_forward<LOGN, true>(t, act, In{srcp}, LdsSpectrum{reg}, reg, REREAD ? reread(tw) : tw);
     }
     __syncthreads();
 
@@ -552,7 +551,7 @@ __device__ __forceinline__ void backward_sq(const ElemOf<St>* __restrict__ x, co
       const bool act = valid && tt < nvalid;
       float2* reg = valid ? xs + (size_t)s * REG : dummy;
       const Out dst{dx + ((act ? tok0 + tt : 0) * QB + j) * (int64_t)N};
-      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, twg);
+      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, REREAD ? reread(tw) : tw);
     }
     __syncthreads();
   }
@@ -963,8 +962,6 @@ bca_forward_wave_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int64_t ngroups
   for (int64_t gi = (int64_t)blockIdx.x * NW + wave; gi < ngroups; gi += wstride) {
     const int64_t tok0 = gi * TW;
     const int nvalid = (int)(tokens - tok0 < TW ? tokens - tok0 : TW);
-    const float2* twg = tw;
-    asm volatile("" : "+s"(twg));
     // (runtime loops over the rounds: unrolled, the compiler hoists every round's loads)
 #pragma unroll 1
     for (int r = 0; r < ROUNDS; ++r) {
@@ -974,7 +971,7 @@ bca_forward_wave_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int64_t ngroups
       const bool act = valid && tt < nvalid;
       float2* reg = valid ? xs + (size_t)s * REG : spare;
       const In src{x + ((act ? tok0 + tt : 0) * QB + j) * (int64_t)N};
-      row_forward<LOGN, true>(t, act, src, LdsSpectrum{reg}, reg, twg);
+      row_forward<LOGN, true>(t, act, src, LdsSpectrum{reg}, reg, reread(tw));
     }
     row_sync<64>();
     static_for<BL>([&](auto bc) {
@@ -1014,7 +1011,7 @@ bca_forward_wave_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int64_t ngroups
       const bool act = valid && tt < nvalid;
       float2* reg = valid ? xs + (size_t)s * REG : spare;
       const Out dst{y + ((act ? tok0 + tt : 0) * QB + i) * (int64_t)N};
-      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, twg);
+      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, reread(tw));
     }
     row_sync<64>();  // the next group's transforms reuse the regions
   }
@@ -1063,8 +1060,6 @@ bca_backward_wave_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int64_t ngroup
   for (int64_t gi = (int64_t)blockIdx.x * NW + wave; gi < ngroups; gi += wstride) {
     const int64_t tok0 = gi * TW;
     const int nvalid = (int)(tokens - tok0 < TW ? tokens - tok0 : TW);
-    const float2* twg = tw;
-    asm volatile("" : "+s"(twg));
 #pragma unroll 1
     for (int r = 0; r < ROUNDS_A; ++r) {
       const int s = r * G + grp;
@@ -1075,7 +1070,7 @@ bca_backward_wave_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int64_t ngroup
       float2* reg = valid ? xs + (size_t)s * REG : spare;
       const ElemOf<St>* base = s < NR ? x : gy;
       const In src{base + ((act ? tok0 + tt : 0) * QB + j) * (int64_t)N};
-      row_forward<LOGN, true>(t, act, src, LdsSpectrum{reg}, reg, twg);
+      row_forward<LOGN, true>(t, act, src, LdsSpectrum{reg}, reg, reread(tw));
     }
     row_sync<64>();
     static_for<BL>([&](auto bc) {
@@ -1118,7 +1113,7 @@ bca_backward_wave_kernel(WavePtrs<St, MAXB> ptrs, int64_t tokens, int64_t ngroup
       const bool act = valid && tt < nvalid;
       float2* reg = valid ? xs + (size_t)s * REG : spare;
       const Out dst{dx + ((act ? tok0 + tt : 0) * QB + j) * (int64_t)N};
-      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, twg);
+      row_inverse<LOGN, true>(t, act, LdsSpectrum{reg}, dst, reg, reread(tw));
     }
     row_sync<64>();
   }
