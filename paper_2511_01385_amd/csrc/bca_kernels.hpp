@@ -861,9 +861,9 @@ static hipError_t bwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t st
 // once per group (from L1/L2: C is small) and, in the backward, keeps its dC_ij[k] sums in
 // registers for the whole kernel.
 //
-// Each group first takes a copy of the twiddle pointer that the compiler cannot see
-// through: otherwise it hoists the loop-invariant twiddle reads of every transform out of
-// the group loop and keeps them all in registers, which spilled.
+// Each transform reads its twiddles anew (reread): otherwise the compiler hoists the
+// loop-invariant twiddle reads of every transform out of the group loop and keeps them all in
+// registers, which spilled.
 template <int LOGN, int QB>
 struct BcaWave {
   using P = RowPlan<LOGN>;

@@ -9,10 +9,9 @@
 // from the hardware sine and cosine of the fraction k/M in revolutions, and a butterfly's
 // higher powers from products, so these plans need no table.
 //
-// What bounds them: VALU issue in 16-bit storage, HBM in float32.  n = 6144 (16 16 12) issues 1010
-// VALU instructions per wave for 12 points a thread, 110 us of issue at 2.4 GHz for 16384 rows, and
-// takes 96 us forward and 116 us inverse in bf16 (4.2 and 3.5 TB/s), 149 us each in float32 (5.4
-// TB/s).  Radices up to 8, always 16 points per thread and the row staged through LDS before its
+// What bounds them: VALU work and the waits between passes in 16-bit storage, HBM in float32.
+// n = 6144 (16 16 12, 12 points a thread, about 1010 VALU instructions per wave), 16384 rows, takes 95
+// us forward and 114 us inverse in bf16 (4.2 and 3.5 TB/s), 149 us each in float32 (5.4 TB/s).  Radices up to 8, always 16 points per thread and the row staged through LDS before its
 // first and after its last pass (five passes, 1740 instructions for 16 points) took 200 and 208 us,
 // 231 and 192 us; 65536 rows of n = 96, each in a workgroup of its own then, 48 us against 9 us.
 #include <hip/hip_runtime.h>
