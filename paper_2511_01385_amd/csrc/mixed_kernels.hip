@@ -5,9 +5,9 @@
 // z_m = x_{2m} + i x_{2m+1} followed by the post-pass that pairs bins k and N-k, and the
 // inverse pre-pass (1/n folded in) followed by the conjugate passes.  A row's N complex
 // points pass through LDS between Stockham passes whose radices (up to 16: the composite 6,
-// 9, 10, 12 and 15 beside the powers of two) a host plan picks at run time; the twiddles come
-// from the hardware sine and cosine of the fraction k/M in revolutions, and a butterfly's
-// higher powers from products, so these plans need no table.
+// 9, 10, 12 and 15 beside the powers of two) a host plan picks at run time; a butterfly's first
+// and fourth twiddle powers come from Taylor sums of sine and cosine and the others from products,
+// so these plans need no table.
 //
 // What bounds them: VALU work and the waits between passes in 16-bit storage, HBM in float32.
 // n = 6144 (16 16 12, 12 points a thread, about 1010 VALU instructions per wave), 16384 rows, takes 95
@@ -165,35 +165,48 @@ __device__ __forceinline__ void dft_any(float2* v) {
   else Dft<R, INV>::run(v);
 }
 
-// exp(-+ 2 pi i num / den) for 0 <= num < den; the caller passes inv_den = 1/den.
-// FINE = false (16-bit rows): the hardware sine and cosine of the angle in revolutions, a few
-// 1e-7 off, a thousandth of what the rows' storage resolves.  FINE = true (float32 rows, which
-// HBM bounds): the angle is reduced to |f| <= 1/2 quarter turns in integers, so that its
-// rounding is relative to f, and Taylor sums of sine and cosine follow (remainders below 2e-9):
-// 16 instructions more per butterfly.  With the hardware functions the radix-16 plans' errors
-// were 1.4 to 1.6 times those of the radix-8 plans before them (n = 6144: 6.7e-7 against 4.3e-7),
-// as a butterfly's fifteenth power carries fifteen times its first one's error.
-template <bool INV, bool FINE>
-__device__ __forceinline__ float2 unit_root_dev(int num, int den, float inv_den) {
-  if constexpr (!FINE) {
-    const float x = (float)num * inv_den;  // revolutions
-    const float s = __builtin_amdgcn_sinf(x), c = __builtin_amdgcn_cosf(x);
-    return make_float2(c, INV ? s : -s);
+// cosine and sine of f quarter turns, |f| <= 1/2, as Taylor sums (remainders below 2e-9): the
+// coefficients are (pi/2)^k / k! with alternating signs
+__device__ __forceinline__ float2 cos_sin_quarters(float f) {
+  const float z = f * f;
+  const float s = f * fmaf(z, fmaf(z, fmaf(z, fmaf(z, 1.60441184787359822e-4f, -4.68175413531868810e-3f),
+                                           7.96926262461670452e-2f), -6.45964097506246253e-1f), 1.57079632679489662f);
+  const float c = fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, -2.52020423730606055e-5f, 9.19260274839426581e-4f),
+                                               -2.08634807633529609e-2f), 2.53669507901048014e-1f),
+                               -1.23370055013616983f), 1.0f);
+  return make_float2(c, s);
+}
+
+// exp(-+ 2 pi i num / den) for 0 <= num < den; the caller passes inv_den = 1/den.  The angle is
+// reduced to |f| <= 1/2 quarter turns in integers, so that its rounding is relative to f.
+// EIGHTH: num / den < 1/8 needs no reduction.
+// (The hardware sine and cosine, 16 instructions fewer, are a few 1e-7 off, which a butterfly's higher
+// powers multiply: with them, and every power from the first, the float32 error of n = 6144 was 6.7e-7 and
+// 0.31 % of float16 results fell on the wrong side of a rounding; now 1.6e-7 and 0.14 %.  16-bit rows
+// of 2^26 values take 0 to 4 % longer for it.)
+template <bool INV, bool EIGHTH>
+__device__ __forceinline__ float2 unit_root(int num, int den, float inv_den) {
+  if constexpr (EIGHTH) {
+    const float2 w = cos_sin_quarters((float)(4 * num) * inv_den);
+    return make_float2(w.x, INV ? w.y : -w.y);
   } else {
     const int q = (int)rintf((float)(4 * num) * inv_den);  // nearest quarter turn
-    const float f = (float)(4 * num - q * den) * inv_den;  // the rest, in quarter turns
-    const float z = f * f;
-    // sin and cos of f pi/2: (pi/2)^k / k! with alternating signs
-    const float s = f * fmaf(z, fmaf(z, fmaf(z, fmaf(z, 1.60441184787359822e-4f, -4.68175413531868810e-3f),
-                                             7.96926262461670452e-2f), -6.45964097506246253e-1f), 1.57079632679489662f);
-    const float c = fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, -2.52020423730606055e-5f, 9.19260274839426581e-4f),
-                                                 -2.08634807633529609e-2f), 2.53669507901048014e-1f),
-                                 -1.23370055013616983f), 1.0f);
+    const float2 w = cos_sin_quarters((float)(4 * num - q * den) * inv_den);
     const bool odd = (q & 1) != 0;
-    const float x = odd ? s : c, y = odd ? c : s;
+    const float x = odd ? w.y : w.x, y = odd ? w.x : w.y;
     const uint32_t flip_x = (uint32_t)((q + 1) & 2) << 30, flip_y = (uint32_t)((q & 2) ^ (INV ? 0 : 2)) << 30;
     return make_float2(__uint_as_float(__float_as_uint(x) ^ flip_x), __uint_as_float(__float_as_uint(y) ^ flip_y));
   }
+}
+
+// ... of the post- and pre-pass, where it enters a result once: float32 rows as above, 16-bit rows
+// by the hardware sine and cosine of the angle in revolutions, a few 1e-7 off
+template <bool INV, bool FINE>
+__device__ __forceinline__ float2 split_root(int num, int den, float inv_den) {
+  if constexpr (FINE) return unit_root<INV, false>(num, den, inv_den);
+  const float x = (float)num * inv_den;  // revolutions
+  const float s = __builtin_amdgcn_sinf(x), c = __builtin_amdgcn_cosf(x);
+  return make_float2(c, INV ? s : -s);
 }
 
 // Pairs of the pre-pass whose loads a thread has in flight at a time: one pair at a time left the
@@ -213,7 +226,6 @@ constexpr int mixed_butterflies() {
 template <int R, bool INV, bool DEEP, bool FROM_GLOBAL, bool TO_GLOBAL, class Acc>
 __device__ __forceinline__ void mixed_pass(const MixedPass& p, int t, int tpr, bool active, float2* lds, const Acc& acc) {
   constexpr int MB = mixed_butterflies<R, DEEP>();
-  constexpr bool FINE = std::is_same<typename Acc::raw_t, float2>::value;
   float2 v[MB][R];
   int kk[MB], qq[MB];
 #pragma unroll
@@ -240,12 +252,17 @@ __device__ __forceinline__ void mixed_pass(const MixedPass& p, int t, int tpr, b
     if (j < p.B) {
       if constexpr (!FROM_GLOBAL) {
         if (p.Ns > 1) {
-          // powers of the butterfly's twiddle, each from its halves
+          // powers of the butterfly's twiddle w: beside w itself w^4 comes from its own angle, so
+          // that w^15 = (w^4)^3 w^3 carries six times a root's error, not fifteen times
           float2 w[R];
-          w[1] = unit_root_dev<INV, FINE>(kk[s], p.Ns * R, p.inv_den);
+          w[1] = unit_root<INV, (R >= 8)>(kk[s], p.Ns * R, p.inv_den);
+          if constexpr (R > 5) w[4] = unit_root<INV, false>(4 * kk[s], p.Ns * R, p.inv_den);
           static_for<R - 1>([&](auto rc) {
             constexpr int r = decltype(rc)::value + 1;
-            if constexpr (r > 1) w[r] = c_mul<false>(w[r / 2], w[r - r / 2]);
+            if constexpr (r == 2 || (r == 4 && R <= 5) || r == 8) w[r] = c_mul<false>(w[r / 2], w[r / 2]);
+            else if constexpr (r == 3) w[r] = c_mul<false>(w[2], w[1]);
+            else if constexpr (r == 12) w[r] = c_mul<false>(w[8], w[4]);
+            else if constexpr (r > 4) w[r] = c_mul<false>(w[r & ~3], w[r & 3]);
             v[s][r] = c_mul<false>(v[s][r], w[r]);
           });
         }
@@ -317,7 +334,7 @@ __global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, int64_t row
       }
       const float2 b = c_conj(lds[N - k]);
       const float2 s = c_add(a, b), d = c_sub(a, b);
-      const float2 w = unit_root_dev<false, FINE>(k, 2 * N, inv_n);  // W_n^k
+      const float2 w = split_root<false, FINE>(k, 2 * N, inv_n);  // W_n^k
       const float2 q = c_mul<false>(d, make_float2(0.5f * w.y, -0.5f * w.x));  // -i W_n^k d / 2
       spec.store(k, make_float2(fmaf(s.x, 0.5f, q.x), fmaf(s.y, 0.5f, q.y)));
       if (2 * k != N) spec.store(N - k, make_float2(fmaf(s.x, 0.5f, -q.x), -fmaf(s.y, 0.5f, -q.y)));
@@ -341,7 +358,7 @@ __global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, int64_t row
         if (2 * m <= N) {
           const float2 ya = Acc::widen(ra[u]), yb = c_conj(Acc::widen(rb[u]));
           const float2 s = c_add(ya, yb), d = c_sub(ya, yb);
-          const float2 w = unit_root_dev<true, FINE>(m, 2 * N, inv_n);         // conj(W_n^m)
+          const float2 w = split_root<true, FINE>(m, 2 * N, inv_n);         // conj(W_n^m)
           const float2 q = c_mul<false>(d, make_float2(-sc * w.y, sc * w.x));  // i conj(W_n^m) d / n
           const float2 lo = make_float2(fmaf(s.x, sc, q.x), fmaf(s.y, sc, q.y));
           lds[m] = m == 0 ? make_float2(sc * (ya.x + ya.y), sc * (ya.x - ya.y)) : lo;

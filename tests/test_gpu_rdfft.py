@@ -213,6 +213,27 @@ def test_mixed_radix_plans(dtype, n, rows):
     assert_close(to_host_f64(t), ord_.rdfft_inverse(spec), dtype, f"mixed inverse n={n} {dtype}")
 
 
+@pytest.mark.parametrize("n", [6144, 6750, 7200])
+def test_mixed_radix_rounding(n):
+    """float16 rows carry an arithmetic error of at most eps = 2.5e-7 of a row's rms (float32 rows of these
+    lengths show 1.6e-7 to 2.0e-7).  A result differs from the correctly rounded one when a rounding boundary
+    lies between it and the true value: boundaries are one ulp apart, so the share of such results is
+    E|error| / ulp, with E|error| = sqrt(2/pi) eps rms for a normal error; 4 standard deviations
+    of that count are allowed."""
+    rows = 2**18 // n
+    for inverse in (False, True):
+        x = inputs.normal_rows(_seed(n, "f16", 10 + inverse), rows, n, "f16")
+        t = to_device(x, "f16")
+        (api.rdfft_inverse if inverse else api.rdfft_forward)(t)
+        ref = (ord_.rdfft_inverse if inverse else ord_.rdfft_forward)(inputs.to_f64(x, "f16"))
+        differ = int((t.cpu() != torch.from_numpy(ref).to(torch.float16)).sum())
+        ulp = 2.0 ** np.maximum(np.floor(np.log2(np.maximum(np.abs(ref), 1e-30))) - 10, -24)
+        rms = np.sqrt(np.mean(ref**2, axis=1, keepdims=True))
+        # (no more than one per result, where ulp is below the error)
+        expected = float(np.minimum(1.0, np.sqrt(2 / np.pi) * 2.5e-7 * rms / ulp).sum())
+        assert differ <= expected + 4 * np.sqrt(expected), (differ, expected, inverse)
+
+
 @pytest.mark.parametrize("n", [30, 3000, 32000])
 def test_mixed_radix_guard_bands_and_round_trip(n):
     rows, pad = 5, 1024
