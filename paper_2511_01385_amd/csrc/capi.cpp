@@ -104,7 +104,7 @@ int transform(void* buf, int64_t rows, int64_t n, int dtype, rdfft_stream_t stre
   if (st != RDFFT_OK) return st;
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e;
-  if (!is_pow2(n)) e = rdfft::launch_mixed_rows(buf, rows, n, dtype, inv, hc, s);
+  if (!is_pow2(n)) e = rdfft::launch_mixed_rows(buf, rows, n, dtype, inv, hc, s, num_cu);
   else if (hc) e = rdfft::launch_rdfft_rows_hc(buf, rows, ilog2(n) - 1, dtype, inv, tw, s);
   else e = rdfft::launch_rdfft_rows(buf, rows, ilog2(n) - 1, dtype, inv, tw, s, num_cu);
   return e == hipSuccess ? RDFFT_OK : RDFFT_ELAUNCH;

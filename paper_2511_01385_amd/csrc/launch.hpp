@@ -36,7 +36,7 @@ hipError_t launch_layout_convert(void* buf, int64_t rows, int logn, bool half16,
 constexpr int64_t kMixedMaxHalf = 16384;
 bool mixed_length_supported(int64_t n);
 hipError_t launch_mixed_rows(void* buf, int64_t rows, int64_t n, int storage, bool inv, bool halfcomplex,
-                             hipStream_t stream);
+                             hipStream_t stream, int num_cu);
 hipError_t launch_mixed_layout(void* buf, int64_t rows, int64_t n, bool half16, bool to_halfcomplex,
                                hipStream_t stream);
 

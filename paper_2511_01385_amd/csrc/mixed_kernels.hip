@@ -10,8 +10,9 @@
 // so these plans need no table.
 //
 // What bounds them: VALU work and the waits between passes in 16-bit storage, HBM in float32.
-// n = 6144 (16 16 12, 12 points a thread, about 1010 VALU instructions per wave), 16384 rows, takes 95
-// us forward and 114 us inverse in bf16 (4.2 and 3.5 TB/s), 149 us each in float32 (5.4 TB/s).  Radices up to 8, always 16 points per thread and the row staged through LDS before its
+// n = 6144 (16 16 12, 12 points a thread, about 1010 VALU instructions per wave), 16384 rows, takes 99
+// us forward and 117 us inverse in bf16 (4.1 and 3.4 TB/s), 149 us each in float32 (5.4 TB/s).  Radices up to
+// 8, always 16 points per thread and the row staged through LDS before its
 // first and after its last pass (five passes, 1740 instructions for 16 points) took 200 and 208 us,
 // 231 and 192 us; 65536 rows of n = 96, each in a workgroup of its own then, 48 us against 9 us.
 #include <hip/hip_runtime.h>
@@ -41,11 +42,12 @@ struct MixedPass {
 struct MixedPlan {
   int n_half;   // N
   int passes;
-  int tpr;      // threads of a row
+  int tpr;      // threads of a row, for the variant that the launch picks
   int log_tpr;  // of a row that shares its workgroup (a power of two), else -1
   int rows_wg;  // rows per workgroup
   int lds_f2;   // LDS slots of a row
-  bool deep;    // a thread holds several butterflies of a pass
+  int waves[3];      // by variant (kHold...): waves of a row's workgroup, 0 where 16 do not do
+  int per_cu[2][3];  // by direction and variant: workgroups per CU
   MixedPass pass[kMixedMaxPasses];
 };
 
@@ -177,36 +179,49 @@ __device__ __forceinline__ float2 cos_sin_quarters(float f) {
   return make_float2(c, s);
 }
 
-// exp(-+ 2 pi i num / den) for 0 <= num < den; the caller passes inv_den = 1/den.  The angle is
-// reduced to |f| <= 1/2 quarter turns in integers, so that its rounding is relative to f.
-// EIGHTH: num / den < 1/8 needs no reduction.
-// (The hardware sine and cosine, 16 instructions fewer, are a few 1e-7 off, which a butterfly's higher
-// powers multiply: with them, and every power from the first, the float32 error of n = 6144 was 6.7e-7 and
-// 0.31 % of float16 results fell on the wrong side of a rounding; now 1.6e-7 and 0.14 %.  16-bit rows
-// of 2^26 values take 0 to 4 % longer for it.)
-template <bool INV, bool EIGHTH>
+// exp(-+ 2 pi i num / den) for 0 <= num < den; the caller passes inv_den = 1/den.  FINE: the angle is reduced to |f| <= 1/2 quarter turns in integers, so that its rounding is
+// relative to f.  Else the hardware sine and cosine of the angle in revolutions, a few 1e-7 off.
+template <bool INV, bool FINE>
 __device__ __forceinline__ float2 unit_root(int num, int den, float inv_den) {
-  if constexpr (EIGHTH) {
-    const float2 w = cos_sin_quarters((float)(4 * num) * inv_den);
-    return make_float2(w.x, INV ? w.y : -w.y);
-  } else {
+  if constexpr (FINE) {
     const int q = (int)rintf((float)(4 * num) * inv_den);  // nearest quarter turn
     const float2 w = cos_sin_quarters((float)(4 * num - q * den) * inv_den);
     const bool odd = (q & 1) != 0;
     const float x = odd ? w.y : w.x, y = odd ? w.x : w.y;
     const uint32_t flip_x = (uint32_t)((q + 1) & 2) << 30, flip_y = (uint32_t)((q & 2) ^ (INV ? 0 : 2)) << 30;
     return make_float2(__uint_as_float(__float_as_uint(x) ^ flip_x), __uint_as_float(__float_as_uint(y) ^ flip_y));
+  } else {
+    const float x = (float)num * inv_den;  // revolutions
+    const float s = __builtin_amdgcn_sinf(x), c = __builtin_amdgcn_cosf(x);
+    return make_float2(c, INV ? s : -s);
   }
 }
 
-// ... of the post- and pre-pass, where it enters a result once: float32 rows as above, 16-bit rows
-// by the hardware sine and cosine of the angle in revolutions, a few 1e-7 off
-template <bool INV, bool FINE>
-__device__ __forceinline__ float2 split_root(int num, int den, float inv_den) {
-  if constexpr (FINE) return unit_root<INV, false>(num, den, inv_den);
-  const float x = (float)num * inv_den;  // revolutions
-  const float s = __builtin_amdgcn_sinf(x), c = __builtin_amdgcn_cosf(x);
-  return make_float2(c, INV ? s : -s);
+// Multiplies input r of a butterfly of radix R by w^r, w = exp(-+ 2 pi i k / (Ns R)), k < Ns.
+// Products carry a root's error once per factor: so w comes from Taylor sums in every storage type
+// (from radix 8 on it lies within 1/8 turn and needs no reduction), and from radix 6 on w^4 is a
+// root of its own, so that w^15 = (w^4)^3 w^3 has six errors, not fifteen.
+// (With the hardware functions for w and all powers from it, n = 6144 had a float32 error of 6.7e-7, and
+// 0.32 % of its float16 results fell on the wrong side of a rounding, plans of radices up to 8 before:
+// 4.3e-7 and 0.22 %; now 1.6e-7 and 0.13 %.  2^26 bf16 values, forward and inverse: 119 and 123 us.)
+template <bool INV, int R>
+__device__ __forceinline__ void twiddle(float2* v, int k, int den, float inv_den) {
+  float2 w[R];
+  if constexpr (R < 8) {
+    w[1] = unit_root<INV, true>(k, den, inv_den);
+  } else {
+    const float2 cs = cos_sin_quarters((float)(4 * k) * inv_den);
+    w[1] = make_float2(cs.x, INV ? cs.y : -cs.y);
+  }
+  if constexpr (R > 5) w[4] = unit_root<INV, true>(4 * k, den, inv_den);
+  static_for<R - 1>([&](auto rc) {
+    constexpr int r = decltype(rc)::value + 1;
+    if constexpr (r == 2 || (r == 4 && R == 5) || r == 8) w[r] = c_mul<false>(w[r / 2], w[r / 2]);
+    else if constexpr (r == 3) w[r] = c_mul<false>(w[2], w[1]);
+    else if constexpr (r == 12) w[r] = c_mul<false>(w[8], w[4]);
+    else if constexpr (r > 4) w[r] = c_mul<false>(w[r & ~3], w[r & 3]);
+    v[r] = c_mul<false>(v[r], w[r]);
+  });
 }
 
 // Pairs of the pre-pass whose loads a thread has in flight at a time: one pair at a time left the
@@ -214,18 +229,18 @@ __device__ __forceinline__ float2 split_root(int num, int den, float inv_den) {
 // post-pass reads LDS and gained nothing from it.
 constexpr int kMixedAhead = 4;
 
-// Butterflies of one pass that a thread can hold: one, or (deep plans, T = 1024 threads) up to
-// ceil(16384 / (1024 R))
-template <int R, bool DEEP>
-constexpr int mixed_butterflies() {
-  return DEEP ? (16 + R - 1) / R : 1;
-}
+// The kernel's variants: butterflies of one pass that a thread can hold.  One; as many as 16
+// values make; or one more where 16 is no multiple of the radix, which fits any row in 1024 threads.
+enum { kHoldOne, kHoldSome, kHoldMany };
+constexpr int held(int R, int hold) { return hold == kHoldOne ? 1 : hold == kHoldSome ? 16 / R : (15 + R) / R; }
+// waves per SIMD that the registers of a variant leave
+constexpr int held_waves(int hold, bool inv) { return hold == kHoldOne ? 7 : hold == kHoldMany ? 4 : inv ? 6 : 5; }
 
 // read(r-th input position) / write as functors of an LDS slot or global pair index; a pass
 // that reads or writes LDS on both sides has a barrier between its reads and its writes.
-template <int R, bool INV, bool DEEP, bool FROM_GLOBAL, bool TO_GLOBAL, class Acc>
+template <int R, bool INV, int HOLD, bool FROM_GLOBAL, bool TO_GLOBAL, class Acc>
 __device__ __forceinline__ void mixed_pass(const MixedPass& p, int t, int tpr, bool active, float2* lds, const Acc& acc) {
-  constexpr int MB = mixed_butterflies<R, DEEP>();
+  constexpr int MB = held(R, HOLD);
   float2 v[MB][R];
   int kk[MB], qq[MB];
 #pragma unroll
@@ -251,21 +266,7 @@ __device__ __forceinline__ void mixed_pass(const MixedPass& p, int t, int tpr, b
     const int j = t + s * tpr;
     if (j < p.B) {
       if constexpr (!FROM_GLOBAL) {
-        if (p.Ns > 1) {
-          // powers of the butterfly's twiddle w: beside w itself w^4 comes from its own angle, so
-          // that w^15 = (w^4)^3 w^3 carries six times a root's error, not fifteen times
-          float2 w[R];
-          w[1] = unit_root<INV, (R >= 8)>(kk[s], p.Ns * R, p.inv_den);
-          if constexpr (R > 5) w[4] = unit_root<INV, false>(4 * kk[s], p.Ns * R, p.inv_den);
-          static_for<R - 1>([&](auto rc) {
-            constexpr int r = decltype(rc)::value + 1;
-            if constexpr (r == 2 || (r == 4 && R <= 5) || r == 8) w[r] = c_mul<false>(w[r / 2], w[r / 2]);
-            else if constexpr (r == 3) w[r] = c_mul<false>(w[2], w[1]);
-            else if constexpr (r == 12) w[r] = c_mul<false>(w[8], w[4]);
-            else if constexpr (r > 4) w[r] = c_mul<false>(w[r & ~3], w[r & 3]);
-            v[s][r] = c_mul<false>(v[s][r], w[r]);
-          });
-        }
+        if (p.Ns > 1) twiddle<INV, R>(v[s], kk[s], p.Ns * R, p.inv_den);
       }
       dft_any<R, INV>(v[s]);
       const int o = (j - kk[s]) * R + kk[s];
@@ -284,21 +285,21 @@ __device__ __forceinline__ void mixed_pass(const MixedPass& p, int t, int tpr, b
   if constexpr (!TO_GLOBAL) __syncthreads();
 }
 
-template <bool INV, bool DEEP, bool FROM_GLOBAL, bool TO_GLOBAL, class Acc>
+template <bool INV, int HOLD, bool FROM_GLOBAL, bool TO_GLOBAL, class Acc>
 __device__ __forceinline__ void mixed_pass_any(const MixedPass& p, int t, int tpr, bool active, float2* lds,
                                                const Acc& acc) {
   switch (p.R) {
-    case 2: mixed_pass<2, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 3: mixed_pass<3, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 4: mixed_pass<4, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 5: mixed_pass<5, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 6: mixed_pass<6, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 8: mixed_pass<8, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 9: mixed_pass<9, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 10: mixed_pass<10, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 12: mixed_pass<12, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    case 15: mixed_pass<15, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
-    default: mixed_pass<16, INV, DEEP, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 2: mixed_pass<2, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 3: mixed_pass<3, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 4: mixed_pass<4, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 5: mixed_pass<5, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 6: mixed_pass<6, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 8: mixed_pass<8, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 9: mixed_pass<9, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 10: mixed_pass<10, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 12: mixed_pass<12, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    case 15: mixed_pass<15, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
+    default: mixed_pass<16, INV, HOLD, FROM_GLOBAL, TO_GLOBAL>(p, t, tpr, active, lds, acc); break;
   }
 }
 
@@ -306,8 +307,9 @@ __device__ __forceinline__ void mixed_pass_any(const MixedPass& p, int t, int tp
 // from global memory and its post-pass writes it; the inverse's pre-pass reads it and its
 // last pass writes it.  Every load of a row precedes its first store (barriers between).
 // HC: the spectrum (the forward's output, the inverse's input) in the halfcomplex layout.
-template <class Acc, class Elem, bool INV, bool HC, bool DEEP>
-__global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, int64_t rows, MixedPlan plan) {
+template <class Acc, class Elem, bool INV, bool HC, int HOLD>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(held_waves(HOLD, INV))))
+mixed_rows_kernel(Elem* buf, int64_t rows, MixedPlan plan) {
   extern __shared__ float2 mixed_lds[];
   constexpr bool FINE = std::is_same<typename Acc::raw_t, float2>::value;
   const int N = plan.n_half, T = plan.tpr;
@@ -320,8 +322,8 @@ __global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, int64_t row
   const Acc sig{rp};                                // the signal pairs (x_{2m}, x_{2m+1})
   const auto spec = spectrum_view<HC, Acc>(rp, N);  // the packed spectrum
   if constexpr (!INV) {
-    mixed_pass_any<INV, DEEP, true, false>(plan.pass[0], t, T, active, lds, sig);
-    for (int q = 1; q < plan.passes; ++q) mixed_pass_any<INV, DEEP, false, false>(plan.pass[q], t, T, active, lds, sig);
+    mixed_pass_any<INV, HOLD, true, false>(plan.pass[0], t, T, active, lds, sig);
+    for (int q = 1; q < plan.passes; ++q) mixed_pass_any<INV, HOLD, false, false>(plan.pass[q], t, T, active, lds, sig);
     if (!active) return;
     // post-pass: Y_k = s/2 + (-i W_n^k / 2) d, Y_{N-k} = conj(s/2 - (-i W_n^k / 2) d) with
     // s = Z_k + conj(Z_{N-k}), d = Z_k - conj(Z_{N-k}); slot 0 = (Y_0, Y_{n/2})
@@ -334,7 +336,7 @@ __global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, int64_t row
       }
       const float2 b = c_conj(lds[N - k]);
       const float2 s = c_add(a, b), d = c_sub(a, b);
-      const float2 w = split_root<false, FINE>(k, 2 * N, inv_n);  // W_n^k
+      const float2 w = unit_root<false, FINE>(k, 2 * N, inv_n);  // W_n^k
       const float2 q = c_mul<false>(d, make_float2(0.5f * w.y, -0.5f * w.x));  // -i W_n^k d / 2
       spec.store(k, make_float2(fmaf(s.x, 0.5f, q.x), fmaf(s.y, 0.5f, q.y)));
       if (2 * k != N) spec.store(N - k, make_float2(fmaf(s.x, 0.5f, -q.x), -fmaf(s.y, 0.5f, -q.y)));
@@ -358,7 +360,7 @@ __global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, int64_t row
         if (2 * m <= N) {
           const float2 ya = Acc::widen(ra[u]), yb = c_conj(Acc::widen(rb[u]));
           const float2 s = c_add(ya, yb), d = c_sub(ya, yb);
-          const float2 w = split_root<true, FINE>(m, 2 * N, inv_n);         // conj(W_n^m)
+          const float2 w = unit_root<true, FINE>(m, 2 * N, inv_n);         // conj(W_n^m)
           const float2 q = c_mul<false>(d, make_float2(-sc * w.y, sc * w.x));  // i conj(W_n^m) d / n
           const float2 lo = make_float2(fmaf(s.x, sc, q.x), fmaf(s.y, sc, q.y));
           lds[m] = m == 0 ? make_float2(sc * (ya.x + ya.y), sc * (ya.x - ya.y)) : lo;
@@ -368,9 +370,26 @@ __global__ void __launch_bounds__(1024) mixed_rows_kernel(Elem* buf, int64_t row
     }
     __syncthreads();
     for (int q = 0; q + 1 < plan.passes; ++q)
-      mixed_pass_any<INV, DEEP, false, false>(plan.pass[q], t, T, active, lds, sig);
-    mixed_pass_any<INV, DEEP, false, true>(plan.pass[plan.passes - 1], t, T, active, lds, sig);
+      mixed_pass_any<INV, HOLD, false, false>(plan.pass[q], t, T, active, lds, sig);
+    mixed_pass_any<INV, HOLD, false, true>(plan.pass[plan.passes - 1], t, T, active, lds, sig);
   }
+}
+
+// The variant for rows with a workgroup each.  What a variant with few butterflies per thread gains in
+// waves it loses in rows per CU, whose passes cover one another's barriers and loads; and its waves
+// are mostly idle but in the pass with the most butterflies.  So: the first variant that holds all
+// rows at once or, beyond that, the one with the most rows per CU, the first among equals.
+// (2^26 float32 values, inverse, one butterfly per thread -- in plans of radices up to 8 and 4 to 16 waves
+// -- by this rule: n = 8000 (5 10 8 10) 176 -- 97 -- 95 us; n = 6250 (fives) 172 -- 107 -- 101 us; n = 9000
+// (15 10 6 5) 190 -- 151 -- 101 us.  Rows per CU are no more than an estimate of the time: n = 5832 bf16 forward
+// takes 95 us by it, 73 with one butterfly per thread.)
+int pick_hold(const int* per_cu, int64_t rows, int num_cu) {
+  int best = kHoldMany;
+  for (int h : {kHoldMany, kHoldSome, kHoldOne}) {
+    if (per_cu[h] == 0) continue;
+    if (per_cu[h] >= per_cu[best] || rows <= (int64_t)num_cu * per_cu[h]) best = h;
+  }
+  return best;
 }
 
 template <class K>
@@ -379,9 +398,9 @@ hipError_t allow_lds(K kernel) {
                              160 * 1024);
 }
 
-template <class Acc, class Elem, bool INV, bool HC, bool DEEP>
+template <class Acc, class Elem, bool INV, bool HC, int HOLD>
 hipError_t launch_mixed_t(void* buf, int64_t rows, const MixedPlan& plan, hipStream_t stream) {
-  static const hipError_t attr = allow_lds(mixed_rows_kernel<Acc, Elem, INV, HC, DEEP>);
+  static const hipError_t attr = allow_lds(mixed_rows_kernel<Acc, Elem, INV, HC, HOLD>);
   if (attr != hipSuccess) return attr;
   const int threads = plan.tpr * plan.rows_wg;
   const size_t lds = (size_t)plan.lds_f2 * plan.rows_wg * sizeof(float2);
@@ -389,7 +408,7 @@ hipError_t launch_mixed_t(void* buf, int64_t rows, const MixedPlan& plan, hipStr
   const int64_t max_rows = kMaxGridThreads / threads * plan.rows_wg;
   for (int64_t r0 = 0; r0 < rows; r0 += max_rows) {
     const int64_t nr = std::min<int64_t>(max_rows, rows - r0);
-    hipLaunchKernelGGL((mixed_rows_kernel<Acc, Elem, INV, HC, DEEP>),
+    hipLaunchKernelGGL((mixed_rows_kernel<Acc, Elem, INV, HC, HOLD>),
                        dim3((unsigned)((nr + plan.rows_wg - 1) / plan.rows_wg)), dim3(threads), lds, stream,
                        base + r0 * plan.n_half, nr, plan);
     const hipError_t e = hipGetLastError();
@@ -398,9 +417,16 @@ hipError_t launch_mixed_t(void* buf, int64_t rows, const MixedPlan& plan, hipStr
   return hipSuccess;
 }
 template <class Acc, class Elem, bool INV, bool HC>
-hipError_t launch_mixed(void* buf, int64_t rows, const MixedPlan& plan, hipStream_t stream) {
-  return plan.deep ? launch_mixed_t<Acc, Elem, INV, HC, true>(buf, rows, plan, stream)
-                   : launch_mixed_t<Acc, Elem, INV, HC, false>(buf, rows, plan, stream);
+hipError_t launch_mixed(void* buf, int64_t rows, const MixedPlan& made, hipStream_t stream, int num_cu) {
+  MixedPlan plan = made;
+  int hold = kHoldOne;
+  if (plan.tpr == 0) {  // rows with a workgroup of their own
+    hold = pick_hold(plan.per_cu[INV], rows, num_cu);
+    plan.tpr = 64 * plan.waves[hold];
+  }
+  if (hold == kHoldOne) return launch_mixed_t<Acc, Elem, INV, HC, kHoldOne>(buf, rows, plan, stream);
+  if (hold == kHoldSome) return launch_mixed_t<Acc, Elem, INV, HC, kHoldSome>(buf, rows, plan, stream);
+  return launch_mixed_t<Acc, Elem, INV, HC, kHoldMany>(buf, rows, plan, stream);
 }
 
 constexpr int kMixedRadices[] = {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
@@ -432,8 +458,8 @@ void best_radices(int n_half, int m, int from, double cost, std::vector<int>* cu
 
 // The plan of N = 2^a 3^b 5^c.  Radices: the cheapest factorisation by VALU instructions.  An
 // odd radix comes first when there is one (its outputs, R apart, then need no padding), the
-// others in falling order.  Threads: one butterfly each in the pass with the most of them (a
-// wave without a butterfly only waits at the barriers), up to 1024; short rows share a workgroup.
+// others in falling order.  Short rows share a workgroup, with one butterfly per thread in the pass
+// with the most of them; longer ones get the threads of each variant of the kernel (pick_hold).
 bool make_plan(int64_t n_half, MixedPlan* plan) {
   if (n_half < 1 || n_half > kMixedMaxHalf || (n_half & (n_half - 1)) == 0) return false;
   int m = (int)n_half;
@@ -452,7 +478,8 @@ bool make_plan(int64_t n_half, MixedPlan* plan) {
     }
   plan->n_half = N;
   plan->passes = (int)radices.size();
-  int Ns = 1, pad_in = 0, max_b = 0, lds = N;
+  int Ns = 1, pad_in = 0, lds = N;
+  int need[3] = {0, 0, 0};  // threads of a row that holds one, some or many butterflies each
   for (int q = 0; q < plan->passes; ++q) {
     MixedPass& p = plan->pass[q];
     const int R = radices[q], M = Ns * R;
@@ -474,23 +501,33 @@ bool make_plan(int64_t n_half, MixedPlan* plan) {
     }
     p.pad_out = pad_in = pad;
     lds = std::max(lds, N + pad * (N / M));
-    max_b = std::max(max_b, p.B);
+    for (int h : {kHoldOne, kHoldSome, kHoldMany}) need[h] = std::max(need[h], (p.B + held(R, h) - 1) / held(R, h));
     Ns = M;
   }
   plan->lds_f2 = lds;
-  int tpr = 1;
-  if (max_b <= 128) {
-    while (tpr < max_b) tpr *= 2;
-  } else {
-    tpr = std::min(1024, (max_b + 63) / 64 * 64);
-  }
-  plan->tpr = tpr;
+  plan->tpr = 0;
   plan->rows_wg = 1;
-  while (plan->rows_wg * 2 * tpr <= 256 && plan->rows_wg * 2 * lds <= kMixedLdsF2 / 4) plan->rows_wg *= 2;
   plan->log_tpr = -1;
-  if (plan->rows_wg > 1)
-    for (plan->log_tpr = 0; (1 << plan->log_tpr) < tpr;) ++plan->log_tpr;
-  plan->deep = max_b > tpr;
+  if (need[kHoldOne] <= 128) {
+    plan->log_tpr = 0;
+    while ((1 << plan->log_tpr) < need[kHoldOne]) ++plan->log_tpr;
+    plan->tpr = 1 << plan->log_tpr;
+    while (plan->rows_wg * 2 * plan->tpr <= 256 && plan->rows_wg * 2 * lds <= kMixedLdsF2 / 4) plan->rows_wg *= 2;
+    return true;
+  }
+  const int by_lds = kMixedLdsF2 / lds;
+  for (int h : {kHoldOne, kHoldSome, kHoldMany}) {
+    int waves = (need[h] + 63) / 64;
+    // (a workgroup's waves are spread evenly over the four SIMDs)
+    auto per_cu = [&](bool inv) {
+      const int held = held_waves(h, inv);
+      return std::min(by_lds, waves < 4 && h != kHoldMany ? 4 * held / waves : held / ((waves + 3) / 4));
+    };
+    // waves that the registers leave beside those workgroups shorten every pass
+    if (h == kHoldMany) waves = std::max(waves, 4 * (held_waves(h, false) / per_cu(false)));
+    plan->waves[h] = waves <= 16 ? waves : 0;
+    for (bool inv : {false, true}) plan->per_cu[inv][h] = waves <= 16 ? per_cu(inv) : 0;
+  }
   return true;
 }
 
@@ -577,10 +614,10 @@ bool mixed_length_supported(int64_t n) {
 }
 
 hipError_t launch_mixed_rows(void* buf, int64_t rows, int64_t n, int storage, bool inv, bool halfcomplex,
-                             hipStream_t stream) {
+                             hipStream_t stream, int num_cu) {
   const MixedPlan* plan = find_plan(n / 2);
   if (plan == nullptr) return hipErrorInvalidValue;
-  using Fn = hipError_t (*)(void*, int64_t, const MixedPlan&, hipStream_t);
+  using Fn = hipError_t (*)(void*, int64_t, const MixedPlan&, hipStream_t, int);
   static const Fn table[2][3][2] = {
       {{&launch_mixed<GlobalF32, float2, false, false>, &launch_mixed<GlobalF32, float2, true, false>},
        {&launch_mixed<GlobalBF16, uint32_t, false, false>, &launch_mixed<GlobalBF16, uint32_t, true, false>},
@@ -588,7 +625,7 @@ hipError_t launch_mixed_rows(void* buf, int64_t rows, int64_t n, int storage, bo
       {{&launch_mixed<GlobalF32, float2, false, true>, &launch_mixed<GlobalF32, float2, true, true>},
        {&launch_mixed<GlobalBF16, uint32_t, false, true>, &launch_mixed<GlobalBF16, uint32_t, true, true>},
        {&launch_mixed<GlobalF16, uint32_t, false, true>, &launch_mixed<GlobalF16, uint32_t, true, true>}}};
-  return table[halfcomplex ? 1 : 0][storage][inv ? 1 : 0](buf, rows, *plan, stream);
+  return table[halfcomplex ? 1 : 0][storage][inv ? 1 : 0](buf, rows, *plan, stream, num_cu);
 }
 
 }  // namespace rdfft

@@ -195,7 +195,10 @@ def test_mixed_radix_parity(n, dtype):
 # with a partial last one, a thread with several butterflies (n = 31250, 32400), both layouts
 @pytest.mark.parametrize("dtype,n,rows", [("f32", 18, 1), ("bf16", 24, 70), ("f32", 50, 33), ("f16", 108, 65),
                                           ("f32", 180, 31), ("bf16", 250, 7), ("f32", 324, 3), ("f32", 1500, 5),
-                                          ("f16", 1536, 3), ("bf16", 7500, 3), ("f32", 31250, 2), ("bf16", 32400, 2)])
+                                          ("f16", 1536, 3), ("bf16", 7500, 3), ("f32", 31250, 2), ("bf16", 32400, 2),
+                                          # rows beyond what one, some butterflies per thread hold at once
+                                          ("bf16", 8000, 400), ("f32", 8000, 1100), ("f16", 6250, 1537),
+                                          ("bf16", 12500, 520), ("f32", 2250, 3100)])
 def test_mixed_radix_plans(dtype, n, rows):
     x = inputs.normal_rows(_seed(n, dtype, 9), rows, n, dtype)
     t = to_device(x, dtype)
