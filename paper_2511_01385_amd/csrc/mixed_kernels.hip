@@ -424,6 +424,9 @@ hipError_t launch_mixed(void* buf, int64_t rows, const MixedPlan& made, hipStrea
     hold = pick_hold(plan.per_cu[INV], rows, num_cu);
     plan.tpr = 64 * plan.waves[hold];
   }
+  // few short rows: no more of them to a workgroup than fill a wave, while some CU has none
+  // (n = 384, 341 float32 rows: 22 workgroups 5.2 us, 86 4.8 us; one row each 6.5 us)
+  while (plan.rows_wg > 1 && plan.rows_wg * plan.tpr > 64 && rows < (int64_t)num_cu * plan.rows_wg) plan.rows_wg /= 2;
   if (hold == kHoldOne) return launch_mixed_t<Acc, Elem, INV, HC, kHoldOne>(buf, rows, plan, stream);
   if (hold == kHoldSome) return launch_mixed_t<Acc, Elem, INV, HC, kHoldSome>(buf, rows, plan, stream);
   return launch_mixed_t<Acc, Elem, INV, HC, kHoldMany>(buf, rows, plan, stream);

@@ -198,7 +198,9 @@ def test_mixed_radix_parity(n, dtype):
                                           ("f16", 1536, 3), ("bf16", 7500, 3), ("f32", 31250, 2), ("bf16", 32400, 2),
                                           # rows beyond what one, some butterflies per thread hold at once
                                           ("bf16", 8000, 400), ("f32", 8000, 1100), ("f16", 6250, 1537),
-                                          ("bf16", 12500, 520), ("f32", 2250, 3100)])
+                                          ("bf16", 12500, 520), ("f32", 2250, 3100),
+                                          # short rows, few and many to a workgroup
+                                          ("f32", 96, 300), ("f16", 96, 9000), ("bf16", 384, 4100)])
 def test_mixed_radix_plans(dtype, n, rows):
     x = inputs.normal_rows(_seed(n, dtype, 9), rows, n, dtype)
     t = to_device(x, dtype)
