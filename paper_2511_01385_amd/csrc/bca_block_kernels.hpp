@@ -206,7 +206,7 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
   const int g0 = wave / HS, h = wave % HS;       // first bin group, share of it
   const int hi = h % S::SI, hj = (h / S::SI) % S::SJ;
   const bool dc_busy = h < S::SI * S::SJ;
-  if (stage != nullptr) {  // the finish kernel, later on the stream, adds into dc
+  if (stage != nullptr) {  // the second stage, later on the stream, adds into dc
     for (int64_t e = (int64_t)blockIdx.x * WG + tid; e < 2 * (int64_t)q * kb * N; e += (int64_t)gridDim.x * WG)
       dc[e] = 0.f;
   }

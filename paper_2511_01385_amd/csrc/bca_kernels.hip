@@ -81,10 +81,11 @@ static hipError_t dc_finish_launch(const FinishPtrs<MAXB>& fp, int count, int ro
   return hipGetLastError();
 }
 
-// The second stage for layers of few, long rows: their units are too few to fill the chip and
-// each thread would wait on many slots' loads in turn (one circulant of p = 8192: 16 units, 16.8
-// us).  Here 64 slots go to a workgroup, whose four waves sum a quarter of the partials each, the
-// sum is stored over dc, and the row kernel inverts it.
+// The second stage for layers of few rows that are longer than the finish kernel's workgroups: its
+// units are too few to fill the chip and each thread would wait on several slots' loads in turn
+// (one circulant of p = 8192: 16 units of 256 threads, 16.8 us).  Here 64 slots go to a workgroup, whose
+// four waves sum a quarter of the partials each, the sum is stored over dc, and the row kernel
+// inverts it.
 constexpr int kSumSlots = 64, kSumWaves = 4;
 __global__ void __launch_bounds__(kSumSlots * kSumWaves)
     bca_dc_sum_kernel(const float2* __restrict__ stage, float* __restrict__ dc, int slots, int chunk, int groups,
@@ -107,6 +108,10 @@ __global__ void __launch_bounds__(kSumSlots * kSumWaves)
   }
 }
 constexpr int kSumMaxUnits = 32;  // units of the finish kernel below which the sum kernel is used
+// ... for rows of more slots than this, which a finish thread would sum one after the other: shorter rows
+// lose more by the second launch (one block of 128, 8192 bf16 tokens, backward: 9.4 us by the finish kernel,
+// 11.8 by two; 2 x 2 blocks of 512, 1021 tokens: 15.3 and 16.6; 2048 and 4096: the same either way)
+constexpr int kSumMinSlots = 2048;
 
 template <int MAXB, int... L>
 static std::array<hipError_t (*)(const FinishPtrs<MAXB>&, int, int, int, int, int64_t, const float2*, hipStream_t),
@@ -119,7 +124,7 @@ hipError_t launch_dc_finish(const float2* stage, float* dc, int rows_ij, int log
                             int64_t tile_f2, const float2* tw, hipStream_t stream) {
   static const auto tab = dc_finish_table<1>(std::make_integer_sequence<int, kBcaMaxLogN + 1>{});
   if (logn < 0 || logn > kBcaMaxLogN) return hipErrorInvalidValue;
-  if (rows_ij * ((groups + kReduceGroup - 1) / kReduceGroup) < kSumMaxUnits) {
+  if ((1 << logn) >= kSumMinSlots && rows_ij * ((groups + kReduceGroup - 1) / kReduceGroup) < kSumMaxUnits) {
     const int slots = rows_ij << logn;
     hipLaunchKernelGGL(bca_dc_sum_kernel, dim3((unsigned)((slots + kSumSlots - 1) / kSumSlots)),
                        dim3(kSumSlots * kSumWaves), 0, stream, stage, dc, slots, chunk, groups, tile_f2);
