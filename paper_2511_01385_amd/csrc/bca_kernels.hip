@@ -63,9 +63,15 @@ __global__ void __launch_bounds__(finish_wg<LOGN>()) bca_dc_finish_kernel(Finish
         if (b < b1 - b0) part[b] = p[b * tile_f2];
       }
     }
-    float2 v = part[0];
-    static_for<kReduceGroup - 1>([&](auto bc) { v = c_add(v, part[decltype(bc)::value + 1]); });
-    reg[lds_pad(k)] = v;
+    // (pairwise: a value passes four additions, not fifteen)
+    static_for<4>([&](auto hc) {
+      constexpr int half = kReduceGroup >> (decltype(hc)::value + 1);
+      static_for<half>([&](auto bc) {
+        constexpr int b = decltype(bc)::value;
+        part[b] = c_add(part[b], part[b + half]);
+      });
+    });
+    reg[lds_pad(k)] = part[0];
   }
   __syncthreads();
   if (threadIdx.x < TPR)  // the whole workgroup when TPR > 64
@@ -108,10 +114,9 @@ __global__ void __launch_bounds__(kSumSlots * kSumWaves)
   }
 }
 constexpr int kSumMaxUnits = 32;  // units of the finish kernel below which the sum kernel is used
-// ... for rows of more slots than this, which a finish thread would sum one after the other: shorter rows
+// ... for rows of kSumMinSlots slots or more: shorter rows
 // lose more by the second launch (one block of 128, 8192 bf16 tokens, backward: 9.4 us by the finish kernel,
 // 11.8 by two; 2 x 2 blocks of 512, 1021 tokens: 15.3 and 16.6; 2048 and 4096: the same either way)
-constexpr int kSumMinSlots = 2048;
 
 template <int MAXB, int... L>
 static std::array<hipError_t (*)(const FinishPtrs<MAXB>&, int, int, int, int, int64_t, const float2*, hipStream_t),

@@ -605,6 +605,8 @@ bca_backward_sq_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __res
 // zeroed dc.
 constexpr int kReduceGroup = 16;
 constexpr int64_t kStageMinAtomics = (int64_t)1 << 21;
+// slots of a row that a finish thread sums one after the other (its workgroups have at most 1024 threads)
+constexpr int kSumMinSlots = 2048;
 hipError_t launch_dc_finish(const float2* stage, float* dc, int rows_ij, int logn, int chunk, int groups,
                             int64_t tile_f2, const float2* tw, hipStream_t stream);
 hipError_t launch_fill_zero(float* p, int64_t count, hipStream_t stream);
@@ -689,23 +691,36 @@ static hipError_t fwd_impl(const BcaArgs& a, const float2* tw, hipStream_t strea
 // LDS of the backward's dC partial sums: q*kb*p/2 pair slots of float2
 static int64_t dc_lds_bytes(int logn, int q, int kb) { return (int64_t)q * kb * ((int64_t)1 << logn) * 8; }
 
+// The general backward's tiles of `ia` x `jb` blocks; TT is 0 when a token does not fit
+struct BwdTiles {
+  int TT;
+  size_t lds;
+  int64_t tiles, grid;
+};
+static BwdTiles bwd_tiles(int logn, int wg, int ia, int jb, int64_t tokens, int num_cu, bool dc) {
+  const int64_t acc_bytes = dc ? dc_lds_bytes(logn, ia, jb) : 0;
+  BwdTiles r{};
+  if (acc_bytes < kLdsLimit) r.TT = tokens_per_tile(logn, jb, ia, tokens, wg, kLdsLimit - (int)acc_bytes);
+  if (r.TT == 0) return r;
+  r.lds = (size_t)(r.TT * (jb + ia) + 1) * region_bytes(logn) + (size_t)acc_bytes;
+  r.tiles = (tokens + r.TT - 1) / r.TT;
+  // persistent workgroups, as many as fit at once: fewer workgroups, fewer dC partials
+  const int per_cu = std::max(1, std::min<int>(kLdsLimit / (int)r.lds, 2048 / wg));
+  r.grid = std::min<int64_t>(r.tiles, (int64_t)num_cu * per_cu);
+  return r;
+}
+
 template <int LOGN, class St>
 static hipError_t bwd_launch(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu, int i0, int ia,
                              int j0, int jb, int mode) {
   constexpr int WG = BcaPlan<LOGN>::BWD_WG;
-  const int64_t acc_bytes = (mode & kBwdDc) ? dc_lds_bytes(LOGN, ia, jb) : 0;
-  const int TT = tokens_per_tile(LOGN, jb, ia, a.tokens, WG, kLdsLimit - (int)acc_bytes);
-  if (TT == 0) return hipErrorInvalidValue;
-  const size_t lds = (size_t)(TT * (jb + ia) + 1) * region_bytes(LOGN) + (size_t)acc_bytes;
+  const BwdTiles r = bwd_tiles(LOGN, WG, ia, jb, a.tokens, num_cu, (mode & kBwdDc) != 0);
+  if (r.TT == 0) return hipErrorInvalidValue;
   static const hipError_t attr = set_lds_limit(bca_backward_kernel<LOGN, St>);
   if (attr != hipSuccess) return attr;
-  const int64_t tiles = (a.tokens + TT - 1) / TT;
-  // persistent workgroups, as many as fit at once: fewer workgroups, fewer dC partials
-  const int per_cu = std::max(1, std::min<int>(kLdsLimit / (int)lds, 2048 / WG));
-  const int64_t grid = std::min<int64_t>(tiles, (int64_t)num_cu * per_cu);
-  hipLaunchKernelGGL((bca_backward_kernel<LOGN, St>), dim3((unsigned)grid), dim3(WG), lds, stream,
+  hipLaunchKernelGGL((bca_backward_kernel<LOGN, St>), dim3((unsigned)r.grid), dim3(WG), r.lds, stream,
                      static_cast<const ElemOf<St>*>(a.x), static_cast<const ElemOf<St>*>(a.c), static_cast<const ElemOf<St>*>(a.y),
-                     static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, a.q, a.kb, i0, ia, j0, jb, mode, TT, tiles, tw);
+                     static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, a.q, a.kb, i0, ia, j0, jb, mode, r.TT, r.tiles, tw);
   return hipGetLastError();
 }
 
@@ -728,11 +743,15 @@ static void dc_chunk(int logn, int q, int kb, int* ia, int* jb) {
   *jb = best_b;
 }
 
+// Whether the dC of all blocks fits in LDS beside a token
+static bool dc_whole(int logn, int wg, int q, int kb, int num_cu) {
+  return bwd_tiles(logn, wg, q, kb, 1, num_cu, true).TT > 0;
+}
+
 template <int LOGN, class St>
 static hipError_t bwd_impl(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu) {
   constexpr int WG = BcaPlan<LOGN>::BWD_WG;
-  const int64_t acc_bytes = dc_lds_bytes(LOGN, a.q, a.kb);
-  if (acc_bytes < kLdsLimit && tokens_per_tile(LOGN, a.kb, a.q, a.tokens, WG, kLdsLimit - (int)acc_bytes) > 0)
+  if (dc_whole(LOGN, WG, a.q, a.kb, num_cu))
     return bwd_launch<LOGN, St>(a, tw, stream, num_cu, 0, a.q, 0, a.kb, kBwdDx | kBwdDc);
   // too many blocks for one LDS-resident dC: dC over block ranges, then the dx path.  The
   // dC launches read gy, and dx may be gy itself, so the dx launch (which reads a tile's gy
@@ -759,10 +778,7 @@ constexpr int kSqMaxBlocks = 4;  // q == kb <= 4
 // tokens for 16 groups, two rounds of each transform (backward of 4096 tokens 26.9 us; 23.6 with
 // 16 tokens).  0 when one token does not fit.
 // The forward spreads over all CUs (the 256-wide layer's 128 tokens: 2 tiles of 64, 7.5 us; 128
-// tiles of 1, 4.0 us).  The backward spreads over 64 workgroups: each adds a dC partial sum, on the
-// same addresses (256-wide, p = 64, 128 tokens: 2 workgroups 15.7 us, 64 workgroups 11.1 us, 128
-// workgroups 12.8 us; p = 32, 512 tokens: 8, 64 and 256 workgroups 11.8, 10.0 and 13.8 us).
-constexpr int kSqBwdSpread = 64;
+// tiles of 1, 4.0 us).
 static int sq_tokens_per_tile(int logn, int rpt, int qb, int spare_rows, int ng, int64_t tokens, int64_t budget,
                               bool* spare, int spread = 0) {
   const int64_t rb = region_bytes(logn);
@@ -815,46 +831,89 @@ constexpr bool sq_fits() {
   return S::BT * S::NSL <= kSqMaxSlots && S::TS <= 8;  // short rows: many threads per bin
 }
 
+constexpr int kSqBwdSpread = 64;
+
+// A measure of the rounding error of dC's sum over the tokens: the float32 additions that follow one
+// another, in a thread (the workgroup's tokens over `phases` threads), between those threads, and between the
+// workgroups: atomics, or the finish kernel's sixteen at a time (pairwise, worth eight in a row) and
+// atomics between these.  The squared error of n equal terms summed in a row grows as n/2.
+static int64_t dc_chain(int64_t tokens, int64_t groups, int phases, bool staged) {
+  const int64_t own = (tokens + groups - 1) / groups;
+  return (own + phases - 1) / phases + std::min<int64_t>(own, phases) +
+         (staged ? kReduceGroup / 2 + (groups + kReduceGroup - 1) / kReduceGroup : groups);
+}
+
+// How the square-layer backward runs a batch
+struct SqBwdRun {
+  int TT;
+  size_t lds;
+  int64_t tiles, grid, tile_f2;
+  int chunk;
+  bool staged;
+  // the same bits on every run: at most two atomic additions to a value of the zeroed dc, which commute
+  bool repeatable() const { return grid <= (staged ? 2 * kReduceGroup : 2); }
+};
+template <int LOGN, class St, int QB, int WG>
+static SqBwdRun sq_bwd_run(const BcaArgs& a, int num_cu, int spread) {
+  using S = BcaSq<LOGN, QB, WG>;
+  constexpr int QKN = QB * QB * S::N;
+  bool spare = false;
+  SqBwdRun r{};
+  // (rows beyond a wave: groups without a row of the inverse round take no region)
+  r.TT = sq_tokens_per_tile(LOGN, 2 * QB, QB, BcaPlan<LOGN>::TPR > 64 ? 2 * QB : QB, WG / BcaPlan<LOGN>::TPR, a.tokens,
+                            kLdsLimit, &spare, spread);
+  if (r.TT == 0) return r;
+  const size_t spectra = (size_t)(r.TT * 2 * QB + (spare ? 1 : 0)) * region_bytes(LOGN);
+  const size_t part = (size_t)S::TS * QKN * sizeof(float2);  // [TS][QB*QB*N]
+  r.lds = std::max(spectra, part);
+  r.tiles = (a.tokens + r.TT - 1) / r.TT;
+  const int per_cu = std::max(1, std::min<int>(kLdsLimit / (int)r.lds, 2048 / WG));
+  r.grid = std::min<int64_t>(r.tiles, (int64_t)num_cu * per_cu);
+  // Two-stage dC sum when dx has its own buffer: each workgroup's partial sums (QKN float2)
+  // fit in the gy rows of its first `chunks` tiles, all of them full tiles
+  const int64_t tile_bytes = (int64_t)r.TT * QB * S::N * (int64_t)sizeof(ElemOf<St>);
+  r.tile_f2 = tile_bytes / (int64_t)sizeof(float2);
+  r.chunk = (int)std::max<int64_t>(1, std::min<int64_t>(QKN, r.tile_f2));
+  const int64_t chunks = (QKN + r.chunk - 1) / r.chunk;
+  // (it saves the fill of dc and makes one launch of the row inverse and the atomics: 11.1 -> 8.9 us for 128
+  // tokens of the 256-wide float32 layer.  Rows that a finish thread sums several slots of gain only
+  // where the atomics are many: one block of 8192, 64 tokens, 20.8 us by atomics, 23.3 staged)
+  r.staged = a.dx != a.y && !a.keep_gy && tile_bytes % (int64_t)sizeof(float2) == 0 && chunks * r.grid <= a.tokens / r.TT &&
+             (S::N < kSumMinSlots || 2 * (int64_t)QKN * r.grid >= kStageMinAtomics);
+  return r;
+}
+
 template <int LOGN, class St, int QB>
 static hipError_t bwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu) {
   constexpr int WG = sq_bwd_wg<LOGN, QB>();
   using S = BcaSq<LOGN, QB, WG>;
-  bool spare = false;
-  // (rows beyond a wave: groups without a row of the inverse round take no region)
-  const int TT = sq_tokens_per_tile(LOGN, 2 * QB, QB, BcaPlan<LOGN>::TPR > 64 ? 2 * QB : QB, WG / BcaPlan<LOGN>::TPR,
-                                    a.tokens, kLdsLimit, &spare, kSqBwdSpread);
-  if (TT == 0) return hipErrorInvalidValue;
-  const size_t spectra = (size_t)(TT * 2 * QB + (spare ? 1 : 0)) * region_bytes(LOGN);
-  const size_t part = (size_t)S::TS * QB * QB * S::N * sizeof(float2);  // [TS][QB*QB*N]
-  const size_t lds = std::max(spectra, part);
-  if (lds > (size_t)kLdsLimit) return hipErrorInvalidValue;
+  constexpr int QKN = QB * QB * S::N;
+  // A short batch spreads over up to 64 workgroups (256-wide, p = 64, 128 tokens: 2 workgroups 15.7 us; 8.9), as
+  // far as dC's error stays within that of the largest tiles, and its bits repeat where theirs do
+  SqBwdRun r = sq_bwd_run<LOGN, St, QB, WG>(a, num_cu, 0);
+  if (r.TT == 0) return hipErrorInvalidValue;
+  const int64_t chain = dc_chain(a.tokens, r.grid, S::TS, r.staged);
+  for (int spread = kSqBwdSpread; spread > 1; spread /= 2) {
+    const SqBwdRun s = sq_bwd_run<LOGN, St, QB, WG>(a, num_cu, spread);
+    if (s.TT < r.TT && dc_chain(a.tokens, s.grid, S::TS, s.staged) <= chain && (s.repeatable() || !r.repeatable())) {
+      r = s;
+      break;
+    }
+  }
+  if (r.lds > (size_t)kLdsLimit) return hipErrorInvalidValue;
   static const hipError_t attr = set_lds_limit(bca_backward_sq_kernel<LOGN, St, QB>);
   if (attr != hipSuccess) return attr;
-  const int64_t tiles = (a.tokens + TT - 1) / TT;
-  const int per_cu = std::max(1, std::min<int>(kLdsLimit / (int)lds, 2048 / WG));
-  const int64_t grid = std::min<int64_t>(tiles, (int64_t)num_cu * per_cu);
-  // Two-stage dC sum when dx has its own buffer: each workgroup's partial sums (QKN float2)
-  // fit in the gy rows of its first `chunks` tiles, all of them full tiles
-  constexpr int QKN = QB * QB * S::N;
-  const int64_t tile_bytes = (int64_t)TT * QB * S::N * (int64_t)sizeof(ElemOf<St>);
-  const int64_t tile_f2 = tile_bytes / (int64_t)sizeof(float2);
-  const int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(QKN, tile_f2));
-  const int64_t chunks = (QKN + chunk - 1) / chunk;
-  // (worth a second launch only when the atomics it replaces are many: 4.2M float32 atomics
-  // for the 4096-wide layer took ~24 us, 0.6M for the 768-wide one less than the launch)
-  const bool staged = a.dx != a.y && !a.keep_gy && tile_bytes % (int64_t)sizeof(float2) == 0 && chunks * grid <= a.tokens / TT &&
-                      2 * (int64_t)QKN * grid >= kStageMinAtomics;
-  float2* const stage = staged ? static_cast<float2*>(a.y) : nullptr;
-  if (!staged) {  // the kernel's atomics add into dc
+  float2* const stage = r.staged ? static_cast<float2*>(a.y) : nullptr;
+  if (!r.staged) {  // the kernel's atomics add into dc
     const hipError_t ez = launch_fill_zero(a.dc, 2 * (int64_t)QKN, stream);
     if (ez != hipSuccess) return ez;
   }
-  hipLaunchKernelGGL((bca_backward_sq_kernel<LOGN, St, QB>), dim3((unsigned)grid), dim3(WG), lds, stream,
+  hipLaunchKernelGGL((bca_backward_sq_kernel<LOGN, St, QB>), dim3((unsigned)r.grid), dim3(WG), r.lds, stream,
                      static_cast<const ElemOf<St>*>(a.x), static_cast<const ElemOf<St>*>(a.c), static_cast<const ElemOf<St>*>(a.y),
-                     static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, TT, tiles, stage, tile_f2, chunk, tw);
+                     static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, r.TT, r.tiles, stage, r.tile_f2, r.chunk, tw);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (staged) return launch_dc_finish(stage, a.dc, QB * QB, LOGN, chunk, (int)grid, tile_f2, tw, stream);
+  if (r.staged) return launch_dc_finish(stage, a.dc, QB * QB, LOGN, r.chunk, (int)r.grid, r.tile_f2, tw, stream);
   // dc holds sum_t conj(X) . G as packed spectra; transform them in place to the time domain
   return launch_rdfft_rows(a.dc, (int64_t)QB * QB, LOGN, kStorageF32, true, tw, stream, num_cu);
 }

@@ -346,6 +346,67 @@ def test_block_kernel_layers(shape):
     _check(x, c, g, dtype, d_out, p, got, f"block {shape}")
 
 
+# dC's sum over the tokens.  Inputs that are one sample at the start of each block have spectra that are that
+# sample in every bin, so that dc_ij[0] = sum_t x_tj g_ti and every other sample is 0, exactly but for the
+# float32 rounding of the bins' sums, whose mean square is (Parseval) the square sum of dc_ij's errors.  n equal terms added in a row have a squared error of n/2 times theirs, u^2 =
+# (2.53e-8)^2 each (a rounding to 24 bits, mean square over a mantissa between 1 and 2); `chain` is the
+# number of additions in a row when the largest tiles run (the tile's tokens over the threads that
+# share a bin, those threads, the workgroups), and no faster split may have more.
+DC_SUM = [
+    # (tokens, d_in, d_out, p, chain): 64-token tiles over 8 threads, 2 workgroups
+    (128, 256, 256, 64, 8 + 8 + 2),
+    (512, 256, 256, 64, 8 + 8 + 8),
+    # 8-token tiles of 4 x 4 blocks of 512, 32 workgroups
+    (256, 2048, 2048, 512, 8 + 1 + 32),
+]
+
+
+def _dc_sum_error(tokens, d_in, d_out, p, mode, runs):
+    q, kb = d_out // p, d_in // p
+    rng = np.random.default_rng(tokens + d_out)
+    c = torch.zeros((q, kb, p), device="cuda")
+    square = 0.0
+    for _ in range(runs):
+        a = rng.standard_normal((tokens, kb)).astype(np.float32)
+        b = rng.standard_normal((tokens, q)).astype(np.float32)
+        x, g = torch.zeros((tokens, kb, p), device="cuda"), torch.zeros((tokens, q, p), device="cuda")
+        x[:, :, 0], g[:, :, 0] = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+        x, g = x.view(tokens, d_in), g.view(tokens, d_out)
+        dx = g if mode == "aliased" else torch.empty_like(x)
+        dc = torch.empty((q, kb, p), device="cuda")
+        (api.bca_backward_keep if mode == "keep" else api.bca_backward)(x, c, g, dx, dc)
+        err = dc.double().cpu().numpy()
+        err[:, :, 0] -= b.astype(np.float64).T @ a.astype(np.float64)
+        square += float(np.mean(np.sum(err**2, axis=2)))
+    return np.sqrt(square / runs / tokens)  # over the rms of the sums
+
+
+@pytest.mark.parametrize("mode", ["apart", "aliased", "keep"])
+@pytest.mark.parametrize("shape", DC_SUM, ids=[f"T{s[0]}_{s[1]}x{s[2]}_p{s[3]}" for s in DC_SUM])
+def test_dc_sum_is_no_longer_chain(shape, mode):
+    tokens, d_in, d_out, p, chain = shape
+    if mode == "aliased" and d_in != d_out:
+        pytest.skip("dx over gy needs a square layer")
+    runs = -(-400 * p * p // (d_in * d_out))  # 400 sums: their rms is within 15 % by 4 standard deviations
+    error = _dc_sum_error(tokens, d_in, d_out, p, mode, runs)
+    # 1.15 for the sample, 1.1 for products that are rounded before they are added
+    assert error <= 1.15 * 1.1 * 2.53e-8 * np.sqrt(chain / 2), error
+
+
+def test_dc_of_two_workgroups_repeats():
+    """A batch of at most two of the largest tiles: two additions to a zeroed dc commute."""
+    tokens, d, p = 128, 256, 64
+    g0, x = torch.randn(tokens, d, device="cuda"), torch.randn(tokens, d, device="cuda")
+    c = torch.randn(d // p, d // p, p, device="cuda")
+    for aliased in (False, True):
+        first = None
+        for _ in range(20):
+            g, dc = g0.clone(), torch.empty_like(c)
+            api.bca_backward(x, c, g, g if aliased else torch.empty_like(x), dc)
+            first = dc if first is None else first
+            assert torch.equal(dc, first)
+
+
 # square layers whose dC slots exceed LDS, with dx == gy: the dC launches read gy, so they
 # must all run before the dx launch overwrites it
 SPLIT_ALIASED = [(5, 4096, 128, "bf16"), (3, 4096, 512, "f32"), (4, 4096, 512, "bf16"), (3, 8192, 1024, "bf16")]
