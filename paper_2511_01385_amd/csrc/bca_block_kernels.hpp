@@ -447,40 +447,90 @@ static hipError_t fwd_block_impl(const BcaArgs& a, const float2* tw, hipStream_t
   return hipGetLastError();
 }
 
+constexpr int kBlockStageMinGrid = 8;
+constexpr int kBlockFewBlocks = 6;
+
+// How the backward runs a batch: tiles of TT tokens
+struct BlockBwdRun {
+  int TT;
+  int64_t tiles, grid, tile_f2, chain;
+  int chunk_rows;
+  bool staged, repeatable;  // repeatable: at most two atomic additions to a value of dc
+  bool general;             // the general kernel is the faster one
+};
+template <int LOGN, class St>
+static BlockBwdRun block_bwd_run(const BcaArgs& a, int num_cu, int TT) {
+  constexpr int N = BcaBlock<LOGN>::N;
+  BlockBwdRun r{};
+  r.TT = TT;
+  r.tiles = (a.tokens + TT - 1) / TT;
+  r.grid = std::min<int64_t>(r.tiles, num_cu);
+  // two-stage dC sum in consumed gy rows (dx apart from gy), as in the square-layer kernels
+  const int64_t blocks = (int64_t)a.q * a.kb, full = a.tokens / TT;
+  r.tile_f2 = (int64_t)TT * a.q * N * (int64_t)sizeof(ElemOf<St>) / (int64_t)sizeof(float2);
+  r.chunk_rows = (int)std::max<int64_t>(1, std::min<int64_t>(blocks, r.tile_f2 / N));
+  const int64_t chunks = (blocks + r.chunk_rows - 1) / r.chunk_rows;
+  // (staged only when every workgroup has whole tiles enough: fewer workgroups that all do cost more
+  // than the atomics, 42 us against 40 us for 16 x 4 blocks of 256 over 2045 tokens; and for enough of
+  // them: with two, 8 tokens of 1 x 2 blocks of 1024, 16.0 us against 14.0.  From eight on it is the faster
+  // one in nearly every layer: 128 tokens 0.78, 4096 tokens 0.75 of the time by atomics)
+  r.staged = a.dx != a.y && !a.keep_gy && r.tile_f2 >= N && r.grid >= kBlockStageMinGrid && chunks * r.grid <= full;
+  r.chain = dc_chain(a.tokens, r.grid, 1, r.staged);
+  r.repeatable = r.grid <= (r.staged ? 2 * kReduceGroup : 2);
+  return r;
+}
+
+// Tokens of the backward's tile: a multiple of four (or a batch of fewer).  At least a CU's share, up to what
+// fills the row groups of the inverse round (one block row of 128 and two columns, 8192 tokens: 39 us with
+// four, 18 us); and more, as far as LDS holds them, until dC's sum has no more additions in a row, and
+// repeats, as in the general kernel with its tiles.
+template <int LOGN, class St, int WG>
+static BlockBwdRun block_bwd_pick(const BcaArgs& a, int num_cu) {
+  using B = BcaBlock<LOGN>;
+  const int64_t ts = (int64_t)block_token_stride<LOGN>(a.q + a.kb) * 8, spare = B::REG * 8;
+  const int most = (int)std::min<int64_t>(64, (kLdsLimit - spare) / ts / 4 * 4);
+  if (a.tokens < 4) return block_bwd_run<LOGN, St>(a, num_cu, (int)a.tokens);
+  constexpr int gwg = BcaPlan<LOGN>::BWD_WG;
+  int ia = a.q, jb = a.kb;
+  if (!dc_whole(LOGN, gwg, a.q, a.kb, num_cu)) dc_chunk(LOGN, a.q, a.kb, &ia, &jb);
+  const BwdTiles general = bwd_tiles(LOGN, gwg, ia, jb, a.tokens, num_cu, true);
+  const int64_t chain = dc_chain(a.tokens, std::max<int64_t>(1, general.grid), 1, false);
+  const int fill = (WG / B::TPR + a.kb - 1) / a.kb;
+  const int64_t share = std::min<int64_t>(fill, (a.tokens + num_cu - 1) / num_cu);
+  int TT = (int)std::min<int64_t>(most, (share + 3) / 4 * 4);
+  BlockBwdRun r = block_bwd_run<LOGN, St>(a, num_cu, TT);
+  while (TT < most && TT < a.tokens && (r.chain > chain || (general.grid <= 2 && !r.repeatable)))
+    r = block_bwd_run<LOGN, St>(a, num_cu, TT += 4);
+  // Few blocks, whose dC sums are four of the sixteen waves' work here: with tiles near the general
+  // kernel's and nothing staged, that one is ahead (1 x 2 blocks of 128, 128 tokens, gy kept: 16.9 us : 27.3)
+  r.general = !r.staged && a.q * a.kb <= kBlockFewBlocks && 4 * r.TT >= 3 * general.TT;
+  return r;
+}
+
 template <int LOGN, class St, int QG, int KG>
 static hipError_t bwd_block_impl(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu) {
   constexpr int WG = block_bwd_wg<LOGN, QG, KG>();
   constexpr int N = BcaBlock<LOGN>::N;
-  const int regions = a.q + a.kb;
-  const int TT = std::min<int>(4, (int)std::max<int64_t>(1, a.tokens));
-  const int TS = block_token_stride<LOGN>(regions);
-  const size_t lds = ((size_t)TT * TS + BcaBlock<LOGN>::REG) * sizeof(float2);
+  const BlockBwdRun r = block_bwd_pick<LOGN, St, WG>(a, num_cu);
+  if (r.general) return hipErrorNotSupported;  // nothing launched: the caller runs the general kernel
+  const int TS = block_token_stride<LOGN>(a.q + a.kb);
+  const size_t lds = ((size_t)r.TT * TS + BcaBlock<LOGN>::REG) * sizeof(float2);
   if (lds > (size_t)kLdsLimit) return hipErrorInvalidValue;
   static const hipError_t attr = set_lds_limit(bca_backward_block_kernel<LOGN, St, QG, KG, WG>);
   if (attr != hipSuccess) return attr;
-  const int64_t tiles = (a.tokens + TT - 1) / TT, full = a.tokens / TT;
-  const int64_t grid = std::min<int64_t>(tiles, num_cu);
-  // two-stage dC sum in consumed gy rows (dx apart from gy), as in the square-layer kernels
-  const int64_t qkn = (int64_t)a.q * a.kb * N;
-  const int64_t tile_f2 = (int64_t)TT * a.q * N * (int64_t)sizeof(ElemOf<St>) / (int64_t)sizeof(float2);
-  const int chunk_rows = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)a.q * a.kb, tile_f2 / N));
-  const int64_t chunks = ((int64_t)a.q * a.kb + chunk_rows - 1) / chunk_rows;
-  // (staged only when every workgroup has whole tiles enough: fewer workgroups that all do cost more
-  // than the atomics, 42 us against 40 us for 16 x 4 blocks of 256 over 2045 tokens)
-  const bool staged = a.dx != a.y && !a.keep_gy && tile_f2 >= N && 2 * qkn * grid >= kStageMinAtomics &&
-                      chunks * grid <= full;
-  float2* const stage = staged ? static_cast<float2*>(a.y) : nullptr;
-  if (!staged) {
-    const hipError_t ez = launch_fill_zero(a.dc, 2 * qkn, stream);
+  float2* const stage = r.staged ? static_cast<float2*>(a.y) : nullptr;
+  if (!r.staged) {
+    const hipError_t ez = launch_fill_zero(a.dc, 2 * (int64_t)a.q * a.kb * N, stream);
     if (ez != hipSuccess) return ez;
   }
-  hipLaunchKernelGGL((bca_backward_block_kernel<LOGN, St, QG, KG, WG>), dim3((unsigned)grid), dim3(WG), lds, stream,
+  hipLaunchKernelGGL((bca_backward_block_kernel<LOGN, St, QG, KG, WG>), dim3((unsigned)r.grid), dim3(WG), lds, stream,
                      static_cast<const ElemOf<St>*>(a.x), static_cast<const ElemOf<St>*>(a.c),
-                     static_cast<const ElemOf<St>*>(a.y), static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, a.q, a.kb, TT,
-                     TS, tiles, stage, tile_f2, chunk_rows, tw);
+                     static_cast<const ElemOf<St>*>(a.y), static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, a.q, a.kb,
+                     r.TT, TS, r.tiles, stage, r.tile_f2, r.chunk_rows, tw);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (staged) return launch_dc_finish(stage, a.dc, a.q * a.kb, LOGN, chunk_rows * N, (int)grid, tile_f2, tw, stream);
+  if (r.staged)
+    return launch_dc_finish(stage, a.dc, a.q * a.kb, LOGN, r.chunk_rows * N, (int)r.grid, r.tile_f2, tw, stream);
   return launch_rdfft_rows(a.dc, (int64_t)a.q * a.kb, LOGN, kStorageF32, true, tw, stream, num_cu);
 }
 

@@ -242,13 +242,12 @@ hipError_t launch_bca_backward(const BcaArgs& a, const float2* tw, hipStream_t s
     if (sq_fn == nullptr) sq_fn = t.sq_bwd[a.q - 1][a.logp - 1];
   }
   if (a.tokens > 0 && sq_fn == nullptr) sq_fn = block_fn(a, true);
-  hipError_t e = hipSuccess;
-  if (sq_fn == nullptr) {
-    e = launch_fill_zero(a.dc, slots, stream);
-    if (e != hipSuccess || a.tokens == 0) return e;
-  }
-  // they also leave dc in the time domain
-  if (sq_fn != nullptr) return sq_fn(a, tw, stream, num_cu);
+  hipError_t e = hipErrorNotSupported;
+  // they also leave dc in the time domain, or leave the call to the general kernel
+  if (sq_fn != nullptr) e = sq_fn(a, tw, stream, num_cu);
+  if (e != hipErrorNotSupported) return e;
+  e = launch_fill_zero(a.dc, slots, stream);
+  if (e != hipSuccess || a.tokens == 0) return e;
   if (a.logp - 1 > kBcaMaxLogN) {
     e = launch_bca_multipass(a, true, tw, stream, num_cu);
   } else {

@@ -335,6 +335,16 @@ BLOCK = [
     (5, 6144, 2048, 1024, "bf16", False),
     (2050, 512, 2048, 128, "bf16", False),
     (2048, 1024, 2048, 256, "f16", False),
+    # tiles of more than four tokens (few blocks), staged and by atomics; more than one tile a workgroup
+    (4100, 256, 128, 128, "bf16", False),
+    (5003, 128, 512, 128, "f32", False),
+    (2045, 256, 384, 128, "f16", False),
+    (1300, 1280, 1280, 256, "f32", True),
+    # a forward or backward left to the general kernel: few rows, few blocks with long tiles, float32 with few tokens
+    (9, 4096, 1024, 1024, "bf16", False),
+    (128, 256, 128, 128, "f32", False),
+    (4097, 512, 128, 128, "f16", False),
+    (33, 6144, 1024, 512, "f32", False),
 ]
 
 
@@ -358,6 +368,9 @@ DC_SUM = [
     (512, 256, 256, 64, 8 + 8 + 8),
     # 8-token tiles of 4 x 4 blocks of 512, 32 workgroups
     (256, 2048, 2048, 512, 8 + 1 + 32),
+    # matrix-core kernels, against the general kernel's tiles: 24 tokens and 43 workgroups; 11 and 93
+    (1021, 256, 1024, 256, 24 + 43),
+    (1021, 1024, 1024, 128, 11 + 93),
 ]
 
 
