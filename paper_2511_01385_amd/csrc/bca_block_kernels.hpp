@@ -415,24 +415,26 @@ constexpr bool block_bwd_fits() {
   return BcaBlockBwd<LOGN, QG, KG, wg>::ACC <= (wg == 1024 ? 48 : 128);
 }
 
-// tokens per tile: a multiple of four up to `most` within `budget` bytes, or fewer than four
-// when the batch is too short to give every CU four; 0 when the tile does not fit
+// Tokens per tile of the forward: a multiple of four up to `most` within `budget` bytes that still
+// gives every CU `per_cu` tiles, or fewer than four when the batch is too short to give every CU four; 0
+// when the tile does not fit.  (One tile per CU, of up to four tokens, comes before a second one: 1021
+// tokens of 12 x 12 blocks of 256, float32, as tiles of two took 29 us, of four 20.)
 template <int LOGN>
-static int block_tile_tokens(int regions, int64_t tokens, int spread, int most, int budget) {
+static int block_tile_tokens(int regions, int64_t tokens, int num_cu, int per_cu, int most, int budget) {
   const int64_t ts = (int64_t)block_token_stride<LOGN>(regions) * 8, spare = BcaBlock<LOGN>::REG * 8;
   int tt = most;
-  while (tt > 4 && (tt * ts + spare > budget || (int64_t)tt * spread > tokens)) tt -= 4;
+  while (tt > 4 && (tt * ts + spare > budget || (int64_t)tt * num_cu * per_cu > tokens)) tt -= 4;
   if (tt * ts + spare > budget) return 0;
-  const int64_t share = std::max<int64_t>(1, (tokens + spread - 1) / spread);
-  return (int)std::min<int64_t>(tt, share < 4 ? share : tt);
+  const int64_t share = std::max<int64_t>(1, (tokens + num_cu - 1) / num_cu);
+  return (int)std::min<int64_t>(tt, share);
 }
 
 template <int LOGN, class St, int KG>
 static hipError_t fwd_block_impl(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu) {
   constexpr int WG = kBlockFwdWG;
   const int regions = std::max(a.q, a.kb);
-  int TT = block_tile_tokens<LOGN>(regions, a.tokens, 2 * num_cu, 16, kLdsLimit / 2);
-  if (TT == 0) TT = block_tile_tokens<LOGN>(regions, a.tokens, num_cu, 4, kLdsLimit);
+  int TT = block_tile_tokens<LOGN>(regions, a.tokens, num_cu, 2, 16, kLdsLimit / 2);
+  if (TT == 0) TT = block_tile_tokens<LOGN>(regions, a.tokens, num_cu, 1, 4, kLdsLimit);
   if (TT == 0) return hipErrorInvalidValue;
   const int TS = block_token_stride<LOGN>(regions);
   const size_t lds = ((size_t)TT * TS + BcaBlock<LOGN>::REG) * sizeof(float2);

@@ -164,14 +164,32 @@ static const BcaStoreTables& store_tables(int storage) {
   return t[storage];
 }
 
+// Whether the general forward is the faster one (its threads read C along the bins, 64 at a time, and
+// waste nothing on few blocks; the matrix-core kernel reads 16 bins of four rows at a time and
+// fills its instructions with four rows and four tokens).  Times general : matrix cores in us, from layers of
+// 1 x 1 to 16 x 16 blocks over 1 to 16384 tokens:
+constexpr int kFwdFewTokens = 2;  // per CU
+static bool general_forward(const BcaArgs& a, int num_cu) {
+  const int p = 1 << a.logp;
+  // few rows: 1021 float32 tokens of 1 x 4 blocks of 1024 8.2 : 10.3, of 2 x 5 12.4 : 13.6
+  if (p == 1024 && a.q <= 2 && (a.kb > a.q || a.tokens < 4)) return true;
+  // one row of short blocks, many tokens: 1 x 2 blocks of 128, 16384 bf16 tokens, 1 : 1.23
+  if (p == 128 && a.q == 1 && a.tokens >= 4096) return true;
+  // float32, C read anew for a token or two: 128 tokens of 12 x 12 blocks of 512 20.6 : 27.7, of 8 x 8
+  // of 1024 16.9 : 20.4; 1021 tokens 45.5 : 35.8 and 42.4 : 34.7
+  return a.storage == kStorageF32 && a.tokens <= kFwdFewTokens * (int64_t)num_cu &&
+         (p == 1024 ? a.kb >= 4 : p == 512 && a.kb > 8);
+}
+
 // The matrix-core kernel for a layer of p = 128 ... 1024 whose spectra of four tokens fit in
 // LDS, or nullptr.
-static BcaBwdFn block_fn(const BcaArgs& a, bool backward) {
+static BcaBwdFn block_fn(const BcaArgs& a, bool backward, int num_cu) {
   static const BcaBlockTables tables[kStorages] = {bca_block_tables_f32(), bca_block_tables_bf16(),
                                                    bca_block_tables_f16()};
   const int logn = a.logp - 1;
   if (logn < kBlockMinLogN || logn > kBlockMaxLogN || a.q > kBlockMaxBlocks || a.kb > kBlockMaxBlocks) return nullptr;
   if (block_lds_bytes(logn, backward ? a.q + a.kb : std::max(a.q, a.kb), 4) > kLdsLimit) return nullptr;
+  if (!backward && general_forward(a, num_cu)) return nullptr;
   const BcaBlockTables& t = tables[a.storage];
   const int ig = block_groups_index(a.q), jg = block_groups_index(a.kb);
   return backward ? t.bwd[logn - kBlockMinLogN][ig][jg] : t.fwd[logn - kBlockMinLogN][jg];
@@ -200,7 +218,7 @@ hipError_t launch_bca_forward(const BcaArgs& a, const float2* tw, hipStream_t st
     if (fn == nullptr) fn = t.sq_fwd[a.q - 1][a.logp - 1];
     if (fn != nullptr) return fn(a, tw, stream, num_cu);
   }
-  if (const BcaBwdFn fn = block_fn(a, false)) return fn(a, tw, stream, num_cu);
+  if (const BcaBwdFn fn = block_fn(a, false, num_cu)) return fn(a, tw, stream, num_cu);
   return t.fwd[a.logp - 1](a, tw, stream);
 }
 
@@ -241,7 +259,7 @@ hipError_t launch_bca_backward(const BcaArgs& a, const float2* tw, hipStream_t s
     sq_fn = t.wave_bwd[a.q - 1][a.logp - 1];
     if (sq_fn == nullptr) sq_fn = t.sq_bwd[a.q - 1][a.logp - 1];
   }
-  if (a.tokens > 0 && sq_fn == nullptr) sq_fn = block_fn(a, true);
+  if (a.tokens > 0 && sq_fn == nullptr) sq_fn = block_fn(a, true, num_cu);
   hipError_t e = hipErrorNotSupported;
   // they also leave dc in the time domain, or leave the call to the general kernel
   if (sq_fn != nullptr) e = sq_fn(a, tw, stream, num_cu);
