@@ -974,18 +974,32 @@ struct WavePtrs {
   float* dc[MAXB];
 };
 
-// Three 3 x 3 blocks of 256 fill six of a wave's eight row slots, and every transform round of
-// the wave kernels runs the other two idle.  With tokens enough for several tiles per workgroup
-// the square-layer kernels in workgroups of two waves do better: five tokens fill 15 of 16
-// slots, the two waves wait only for each other, and each thread keeps its bin's C (and dC).
-// One layer of 98304 tokens, bf16: forward 137 -> 112 us, backward 247 -> 217 us; of 32768: 46 -> 40
-// and 86 -> 83 us; of 4096 (less than a tile each): 8.4 -> 8.8 us.  1, 2 and 4 blocks fill the wave
-// kernels' rounds, which are then the faster ones (backward of 1 x 1: 67 us against 106).
+// Three blocks a side leave two of a wave's eight row slots idle in every transform round of the wave
+// kernels (p = 128 and 256).  With tokens enough for several tiles per workgroup the square-layer kernels in
+// workgroups of two waves do better: five tokens fill 15 of 16 slots, the two waves wait only for each
+// other, and each thread keeps its bin's C (and dC).  Wave : pair kernels in us, 3 x 3 blocks of 256:
+// forward, 16384 tokens 21 : 20 (one layer, bf16) and 21 : 23 (four), 24576 in twelve 35 : 30, 41 : 34 (float32),
+// 49152 65 : 53, 105 : 71; backward, 32768 tokens 72 : 71, 98 : 93, 49152 109 : 96, 159 : 133, 98304 251 : 205.
+// Blocks of 128: backward, 16384 tokens 25 : 29, 49152 66 : 61, 71 : 65, 98304 126 : 113, but forward,
+// 49152 28.9 : 30.0: two threads share a bin there and Y cannot take X's place in LDS.  1, 2 and 4 blocks fill
+// the wave kernels' rounds, which are then the faster ones (backward of 1 x 1: 67 us against 106).
 constexpr int kPairWG = 128, kPairTokens = 5;
-constexpr int kPairFwdPerCu = 8, kPairBwdPerCu = 4;  // workgroups per CU
 constexpr int64_t kPairFwdMinTokens = 24576, kPairBwdMinTokens = 49152;  // of all layers of a launch
 template <int LOGN, int QB>
-constexpr bool pair_layer() { return LOGN == 7 && QB == 3; }
+constexpr bool pair_layer(bool backward) {  // a wave's rows leave row slots idle; forward: a bin has its thread
+  return wave_fits<LOGN, QB>(true) && (wave_tokens<LOGN, QB>() * QB) % BcaWave<LOGN, QB>::G != 0 &&
+         (backward || BcaWave<LOGN, QB>::N >= kPairWG);
+}
+template <int LOGN, int QB>
+constexpr size_t pair_lds_bytes(bool backward) {
+  return (size_t)(kPairTokens * (backward ? 2 : 1) * QB + 1) * BcaPlan<LOGN>::REGION * sizeof(float2);
+}
+// workgroups per CU
+template <int LOGN, int QB>
+constexpr int pair_per_cu(bool backward) {
+  const int most = backward ? 4 : 8, by_lds = kLdsLimit / (int)pair_lds_bytes<LOGN, QB>(backward);
+  return by_lds < most ? by_lds : most;
+}
 
 template <int LOGN, class St, int QB, int MAXB>
 __global__ void __launch_bounds__(kPairWG) __attribute__((amdgpu_waves_per_eu(4)))
@@ -1224,12 +1238,11 @@ constexpr size_t wave_lds_bytes(bool backward) {
 template <int LOGN, class St, int QB, int MAXB>
 static hipError_t fwd_wave_launch(const WavePtrs<St, MAXB>& ptrs, int count, int64_t tokens, const float2* tw,
                                   hipStream_t stream, int num_cu) {
-  if constexpr (pair_layer<LOGN, QB>()) {
+  if constexpr (pair_layer<LOGN, QB>(false)) {
     if (tokens * count >= kPairFwdMinTokens) {
-      constexpr size_t lds = (size_t)(kPairTokens * QB + 1) * BcaPlan<LOGN>::REGION * sizeof(float2);
-      static_assert(lds * kPairFwdPerCu <= (size_t)kLdsLimit, "tokens too many for LDS");
+      constexpr size_t lds = pair_lds_bytes<LOGN, QB>(false);
       const int64_t tiles = (tokens + kPairTokens - 1) / kPairTokens;
-      const int64_t grid = std::min<int64_t>(tiles, ((int64_t)num_cu * kPairFwdPerCu + count - 1) / count);
+      const int64_t grid = std::min<int64_t>(tiles, ((int64_t)num_cu * pair_per_cu<LOGN, QB>(false) + count - 1) / count);
       hipLaunchKernelGGL((bca_forward_pair_kernel<LOGN, St, QB, MAXB>), dim3((unsigned)grid, (unsigned)count),
                          dim3(kPairWG), lds, stream, ptrs, tokens, kPairTokens, tiles, tw);
       return hipGetLastError();
@@ -1305,16 +1318,15 @@ static hipError_t bwd_wave_launch(const WavePtrs<St, MAXB>& ptrs, int count, boo
   // valid tokens)
   const int64_t region_f2 = (int64_t)NW * TW * QB * W::N * (int64_t)sizeof(ElemOf<St>) / (int64_t)sizeof(float2);
   const bool staged = apart && region_f2 >= QKN && grid * NW * TW <= tokens;
-  if constexpr (pair_layer<LOGN, QB>()) {
+  if constexpr (pair_layer<LOGN, QB>(true)) {
     const int64_t tiles = (tokens + kPairTokens - 1) / kPairTokens;
     const int64_t tile_f2 = (int64_t)kPairTokens * QB * W::N * (int64_t)sizeof(ElemOf<St>) / (int64_t)sizeof(float2);
     const int chunk = (int)std::min<int64_t>(QKN, tile_f2);
     const int64_t chunks = (QKN + chunk - 1) / chunk;
-    const int64_t pgrid = std::min<int64_t>(tiles, std::max<int64_t>(1, (int64_t)num_cu * kPairBwdPerCu / count));
+    const int64_t pgrid = std::min<int64_t>(tiles, std::max<int64_t>(1, (int64_t)num_cu * pair_per_cu<LOGN, QB>(true) / count));
     if (apart && tokens * count >= kPairBwdMinTokens && chunks * pgrid <= tokens / kPairTokens) {
-      constexpr size_t plds = (size_t)(kPairTokens * 2 * QB + 1) * BcaPlan<LOGN>::REGION * sizeof(float2);
-      static_assert(plds * kPairBwdPerCu <= (size_t)kLdsLimit, "tokens too many for LDS");
-      static_assert(plds >= (size_t)QKN * sizeof(float2), "the partial sums pass through the spectra's LDS");
+      constexpr size_t plds = pair_lds_bytes<LOGN, QB>(true);
+      static_assert(plds >= (size_t)BcaSq<LOGN, QB, kPairWG>::TS * QKN * sizeof(float2), "the partial sums pass through the spectra's LDS");
       hipLaunchKernelGGL((bca_backward_pair_kernel<LOGN, St, QB, MAXB>), dim3((unsigned)pgrid, (unsigned)count),
                          dim3(kPairWG), plds, stream, ptrs, tokens, kPairTokens, tiles, tile_f2, chunk, tw);
       const hipError_t ep = hipGetLastError();

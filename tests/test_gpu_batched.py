@@ -80,7 +80,9 @@ def _init():
 FUSED = [(24, 256, 768, 256, "bf16"), (40, 64, 256, 128, "bf16"), (5, 256, 1024, 512, "f16"),
          (3, 100, 512, 128, "f32"),  # a forward side by side, a backward too short to stage
          (17, 203, 128, 128, "bf16"),  # staged by fewer workgroups than would fit, with a ragged end
-         (16, 3077, 768, 256, "bf16")]  # tokens enough for the two-wave workgroups, a ragged last tile
+         # tokens enough for the two-wave workgroups, a ragged last tile
+         (16, 3077, 768, 256, "bf16"), (12, 4101, 768, 256, "f16"), (13, 3803, 768, 256, "f32"),
+         (24, 2051, 384, 128, "f32"), (8, 6203, 384, 128, "bf16")]
 
 
 @pytest.mark.parametrize("shape", FUSED, ids=[f"n{s[0]}_T{s[1]}_{s[2]}_p{s[3]}_{s[4]}" for s in FUSED])

@@ -316,6 +316,19 @@ def test_wave_kernel_layers(shape):
     _check(x, c, g, dtype, d, p, got, f"wave {shape}")
 
 
+# one layer of 3 x 3 blocks over tokens enough for the two-wave workgroups (forward 24576, backward 49152), a
+# ragged last tile; y over x
+PAIR = [(24577, 768, 256, "f16", True), (49153, 768, 256, "bf16", True), (49157, 384, 128, "f32", False)]
+
+
+@pytest.mark.parametrize("shape", PAIR, ids=[f"T{s[0]}_{s[1]}_p{s[2]}_{s[3]}" for s in PAIR])
+def test_pair_kernel_layers(shape):
+    tokens, d, p, dtype, alias_y = shape
+    x, c, g = _problem(3131 + tokens, tokens, d, d, p, 0.02, dtype)
+    got = _run(x, c, g, dtype, d, alias_y=alias_y)
+    _check(x, c, g, dtype, d, p, got, f"pair {shape}")
+
+
 # the matrix-core kernels (p = 128 ... 1024, up to 16 x 16 blocks, not the square layers of at most
 # 4 x 4): block counts that leave part of a group of four, tiles of fewer than four tokens, ragged
 # last tiles, dc by atomics and staged (2048 tokens and more; with a ragged end), dx over gy
