@@ -329,6 +329,20 @@ def test_pair_kernel_layers(shape):
     _check(x, c, g, dtype, d, p, got, f"pair {shape}")
 
 
+# square layers whose backward takes 1024 threads: tiles of several tokens, more than one of them for a
+# workgroup, dc staged and by atomics, dx over gy
+WIDE_SQUARE = [(1100, 4096, 4096, "bf16", False), (1033, 8192, 4096, "f16", False), (1100, 4096, 4096, "f32", True),
+               (530, 8192, 8192, "bf16", True), (700, 6144, 2048, "bf16", False)]
+
+
+@pytest.mark.parametrize("shape", WIDE_SQUARE, ids=[f"T{s[0]}_{s[1]}_p{s[2]}_{s[3]}{'_aliased' if s[4] else ''}" for s in WIDE_SQUARE])
+def test_wide_square_layers(shape):
+    tokens, d, p, dtype, alias = shape
+    x, c, g = _problem(3232 + tokens, tokens, d, d, p, 0.01, dtype)
+    got = _run(x, c, g, dtype, d, alias_dx=alias)
+    _check(x, c, g, dtype, d, p, got, f"wide square {shape}")
+
+
 # the matrix-core kernels (p = 128 ... 1024, up to 16 x 16 blocks, not the square layers of at most
 # 4 x 4): block counts that leave part of a group of four, tiles of fewer than four tokens, ragged
 # last tiles, dc by atomics and staged (2048 tokens and more; with a ragged end), dx over gy
