@@ -408,11 +408,20 @@ template <int LOGN, int QG, int KG>
 constexpr int block_bwd_wg() {
   return BcaBlockBwd<LOGN, QG, KG, 1024>::ACC <= 48 ? 1024 : 512;
 }
-// built when the dC registers leave room for the transforms (128 or 256 registers per lane)
+// whether LDS holds four tokens of `regions` spectra and a spare region
+template <int LOGN>
+constexpr bool block_tile_fits(int regions) {
+  return (4 * block_token_stride<LOGN>(regions) + BcaBlock<LOGN>::REG) * (int)sizeof(float2) <= kLdsLimit;
+}
+constexpr int fewest_blocks(int G) { return G == 1 ? 1 : G == 2 ? 5 : 9; }  // of a layer of G groups
+
+// built when the dC registers leave room for the transforms (128 or 256 registers per lane), and LDS for a
+// tile of the fewest blocks
 template <int LOGN, int QG, int KG>
 constexpr bool block_bwd_fits() {
   constexpr int wg = block_bwd_wg<LOGN, QG, KG>();
-  return BcaBlockBwd<LOGN, QG, KG, wg>::ACC <= (wg == 1024 ? 48 : 128);
+  return BcaBlockBwd<LOGN, QG, KG, wg>::ACC <= (wg == 1024 ? 48 : 128) &&
+         block_tile_fits<LOGN>(fewest_blocks(QG) + fewest_blocks(KG));
 }
 
 // Tokens per tile of the forward: a multiple of four up to `most` within `budget` bytes that still
@@ -547,9 +556,14 @@ static constexpr std::array<std::array<BcaBwdFn, 3>, 3> block_bwd_entries() {
            {block_bwd_entry<LOGN, St, 2, 1>(), block_bwd_entry<LOGN, St, 2, 2>(), block_bwd_entry<LOGN, St, 2, 4>()},
            {block_bwd_entry<LOGN, St, 4, 1>(), block_bwd_entry<LOGN, St, 4, 2>(), block_bwd_entry<LOGN, St, 4, 4>()}}};
 }
+template <int LOGN, class St, int KG>
+static constexpr BcaBwdFn block_fwd_entry() {
+  if constexpr (block_tile_fits<LOGN>(fewest_blocks(KG))) return &fwd_block_impl<LOGN, St, KG>;
+  else return nullptr;
+}
 template <int LOGN, class St>
 static constexpr std::array<BcaBwdFn, 3> block_fwd_entries() {
-  return {&fwd_block_impl<LOGN, St, 1>, &fwd_block_impl<LOGN, St, 2>, &fwd_block_impl<LOGN, St, 4>};
+  return {block_fwd_entry<LOGN, St, 1>(), block_fwd_entry<LOGN, St, 2>(), block_fwd_entry<LOGN, St, 4>()};
 }
 
 // [logn - kBlockMinLogN][input groups] and [logn - kBlockMinLogN][output groups][input groups]
