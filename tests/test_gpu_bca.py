@@ -51,10 +51,12 @@ SMALL = [
     (5, 8192, 8192, 4096, "f32"),
     (4, 6144, 6144, 2048, "bf16"),
     (9, 256, 256, 16, "f32"),
-    # layers whose dC slots exceed LDS: dC over block ranges, then one dx launch
+    # layers whose dC slots exceed LDS: dC over block ranges, then one dx launch (8 x 16 blocks of 256:
+    # in the matrix-core kernel's registers)
     (5, 4096, 4096, 128, "bf16"),
     (3, 2048, 4096, 64, "f32"),
     (7, 4096, 2048, 256, "f32"),
+    (4, 8192, 4096, 1024, "f32"),
     # a token's spectra beyond the forward's two-workgroups-per-CU budget (8 x 8 blocks of 1024)
     (3, 8192, 8192, 1024, "bf16"),
     (2, 8192, 8192, 1024, "f32"),
@@ -448,8 +450,10 @@ def test_dc_of_two_workgroups_repeats():
 
 
 # square layers whose dC slots exceed LDS, with dx == gy: the dC launches read gy, so they
-# must all run before the dx launch overwrites it
-SPLIT_ALIASED = [(5, 4096, 128, "bf16"), (3, 4096, 512, "f32"), (4, 4096, 512, "bf16"), (3, 8192, 1024, "bf16")]
+# must all run before the dx launch overwrites it (8 x 8 blocks of 512 hold their sums in the matrix-core
+# kernel's registers instead, which reads a tile's gy before it writes the tile's dx)
+SPLIT_ALIASED = [(5, 4096, 128, "bf16"), (3, 4096, 512, "f32"), (4, 4096, 512, "bf16"), (3, 8192, 1024, "bf16"),
+                 (2, 8192, 1024, "f32"), (3, 8192, 1024, "f16"), (5, 8192, 512, "f32"), (3, 2560, 128, "f16")]
 
 
 @pytest.mark.parametrize("shape", SPLIT_ALIASED, ids=[f"T{s[0]}_{s[1]}_p{s[2]}_{s[3]}" for s in SPLIT_ALIASED])
