@@ -883,11 +883,37 @@ static SqBwdRun sq_bwd_run(const BcaArgs& a, int num_cu, int spread) {
   return r;
 }
 
+template <int LOGN, class St, int QB, int WG>
+static hipError_t bwd_sq_launch(const BcaArgs& a, const SqBwdRun& r, const float2* tw, hipStream_t stream, int num_cu) {
+  constexpr int QKN = QB * QB * BcaSq<LOGN, QB, WG>::N;
+  if (r.TT == 0 || r.lds > (size_t)kLdsLimit) return hipErrorInvalidValue;
+  static const hipError_t attr = set_lds_limit(bca_backward_sq_kernel<LOGN, St, QB, WG>);
+  if (attr != hipSuccess) return attr;
+  float2* const stage = r.staged ? static_cast<float2*>(a.y) : nullptr;
+  if (!r.staged) {  // the kernel's atomics add into dc
+    const hipError_t ez = launch_fill_zero(a.dc, 2 * (int64_t)QKN, stream);
+    if (ez != hipSuccess) return ez;
+  }
+  hipLaunchKernelGGL((bca_backward_sq_kernel<LOGN, St, QB, WG>), dim3((unsigned)r.grid), dim3(WG), r.lds, stream,
+                     static_cast<const ElemOf<St>*>(a.x), static_cast<const ElemOf<St>*>(a.c), static_cast<const ElemOf<St>*>(a.y),
+                     static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, r.TT, r.tiles, stage, r.tile_f2, r.chunk, tw);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (r.staged) return launch_dc_finish(stage, a.dc, QB * QB, LOGN, r.chunk, (int)r.grid, r.tile_f2, tw, stream);
+  // dc holds sum_t conj(X) . G as packed spectra; transform them in place to the time domain
+  return launch_rdfft_rows(a.dc, (int64_t)QB * QB, LOGN, kStorageF32, true, tw, stream, num_cu);
+}
+
 template <int LOGN, class St, int QB>
 static hipError_t bwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t stream, int num_cu) {
-  constexpr int WG = sq_bwd_wg<LOGN, QB>();
+  constexpr int WG = sq_bwd_wg<LOGN, QB>(), PLAN_WG = BcaPlan<LOGN>::BWD_WG, TPR = BcaPlan<LOGN>::TPR;
   using S = BcaSq<LOGN, QB, WG>;
-  constexpr int QKN = QB * QB * S::N;
+  if constexpr (WG != PLAN_WG && TPR > 64) {
+    // a token whose transforms are one round of the plan's threads anyway: more of them only wait
+    // (one block of 4096 15.8 us, 16.7 in 1024 threads; 2 x 2 19.1 and 20.7)
+    if (a.tokens * 2 * QB <= PLAN_WG / TPR)
+      return bwd_sq_launch<LOGN, St, QB, PLAN_WG>(a, sq_bwd_run<LOGN, St, QB, PLAN_WG>(a, num_cu, 0), tw, stream, num_cu);
+  }
   // A short batch spreads over up to 64 workgroups (256-wide, p = 64, 128 tokens: 2 workgroups 15.7 us; 8.9), as
   // far as dC's error stays within that of the largest tiles, and its bits repeat where theirs do
   SqBwdRun r = sq_bwd_run<LOGN, St, QB, WG>(a, num_cu, 0);
@@ -900,22 +926,7 @@ static hipError_t bwd_sq_impl(const BcaArgs& a, const float2* tw, hipStream_t st
       break;
     }
   }
-  if (r.lds > (size_t)kLdsLimit) return hipErrorInvalidValue;
-  static const hipError_t attr = set_lds_limit(bca_backward_sq_kernel<LOGN, St, QB>);
-  if (attr != hipSuccess) return attr;
-  float2* const stage = r.staged ? static_cast<float2*>(a.y) : nullptr;
-  if (!r.staged) {  // the kernel's atomics add into dc
-    const hipError_t ez = launch_fill_zero(a.dc, 2 * (int64_t)QKN, stream);
-    if (ez != hipSuccess) return ez;
-  }
-  hipLaunchKernelGGL((bca_backward_sq_kernel<LOGN, St, QB>), dim3((unsigned)r.grid), dim3(WG), r.lds, stream,
-                     static_cast<const ElemOf<St>*>(a.x), static_cast<const ElemOf<St>*>(a.c), static_cast<const ElemOf<St>*>(a.y),
-                     static_cast<ElemOf<St>*>(a.dx), a.dc, a.tokens, r.TT, r.tiles, stage, r.tile_f2, r.chunk, tw);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (r.staged) return launch_dc_finish(stage, a.dc, QB * QB, LOGN, r.chunk, (int)r.grid, r.tile_f2, tw, stream);
-  // dc holds sum_t conj(X) . G as packed spectra; transform them in place to the time domain
-  return launch_rdfft_rows(a.dc, (int64_t)QB * QB, LOGN, kStorageF32, true, tw, stream, num_cu);
+  return bwd_sq_launch<LOGN, St, QB, WG>(a, r, tw, stream, num_cu);
 }
 
 // ----------------------------------------------------------------------------------
