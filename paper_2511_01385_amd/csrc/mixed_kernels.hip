@@ -18,7 +18,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <vector>
 
 #include "fft_device.hpp"
 #include "launch.hpp"
@@ -441,21 +440,27 @@ double butterfly_cost(int R) {
   return dft[R] + 8.0 * (R - 1) + 2.0 * R + 30.0;
 }
 
+// Radices of a plan (fixed storage: plans are made inside the C entry points, which must not throw)
+struct Radices {
+  int count = 0;
+  int r[kMixedMaxPasses];
+};
+
 // The cheapest factorisation of m into radices no larger than kMixedRadices[from] (largest first)
-void best_radices(int n_half, int m, int from, double cost, std::vector<int>* cur, std::vector<int>* best,
-                  double* best_cost) {
+void best_radices(int n_half, int m, int from, double cost, Radices* cur, Radices* best, double* best_cost) {
   if (cost >= *best_cost) return;
   if (m == 1) {
     *best = *cur;
     *best_cost = cost;
     return;
   }
+  if (cur->count == kMixedMaxPasses) return;
   for (int i = from; i < (int)(sizeof(kMixedRadices) / sizeof(int)); ++i) {
     const int R = kMixedRadices[i];
     if (m % R != 0) continue;
-    cur->push_back(R);
+    cur->r[cur->count++] = R;
     best_radices(n_half, m / R, i, cost + (double)(n_half / R) * butterfly_cost(R), cur, best, best_cost);
-    cur->pop_back();
+    --cur->count;
   }
 }
 
@@ -470,22 +475,22 @@ bool make_plan(int64_t n_half, MixedPlan* plan) {
     while (m % f == 0) m /= f;
   if (m != 1) return false;
   const int N = (int)n_half;
-  std::vector<int> cur, radices;
+  Radices cur, radices;
   double cost = 1e30;
   best_radices(N, N, 0, 0.0, &cur, &radices, &cost);
-  if (radices.empty() || (int)radices.size() > kMixedMaxPasses) return false;
-  for (size_t i = 0; i < radices.size(); ++i)
-    if (radices[i] & 1) {
-      std::swap(radices[0], radices[i]);
+  if (radices.count == 0) return false;
+  for (int i = 0; i < radices.count; ++i)
+    if (radices.r[i] & 1) {
+      std::swap(radices.r[0], radices.r[i]);
       break;
     }
   plan->n_half = N;
-  plan->passes = (int)radices.size();
+  plan->passes = radices.count;
   int Ns = 1, pad_in = 0, lds = N;
   int need[3] = {0, 0, 0};  // threads of a row that holds one, some or many butterflies each
   for (int q = 0; q < plan->passes; ++q) {
     MixedPass& p = plan->pass[q];
-    const int R = radices[q], M = Ns * R;
+    const int R = radices.r[q], M = Ns * R;
     p.R = R;
     p.B = N / R;
     p.Ns = Ns;
@@ -535,21 +540,22 @@ bool make_plan(int64_t n_half, MixedPlan* plan) {
 }
 
 // The plans of all supported lengths, made once
+constexpr int kMixedLengths = 186;  // 2^a 3^b 5^c up to kMixedMaxHalf but the powers of two
+struct MixedPlans {
+  int count = 0;
+  MixedPlan plan[kMixedLengths];
+};
 const MixedPlan* find_plan(int64_t n_half) {
-  static const std::vector<MixedPlan> plans = [] {
-    std::vector<MixedPlan> v;
-    for (int64_t h = 1; h <= kMixedMaxHalf; ++h) {
-      int64_t m = h;
-      for (int f : {2, 3, 5})
-        while (m % f == 0) m /= f;
-      MixedPlan p;
-      if (m == 1 && make_plan(h, &p)) v.push_back(p);
-    }
+  static const MixedPlans plans = [] {
+    MixedPlans v;
+    for (int64_t h = 1; h <= kMixedMaxHalf && v.count < kMixedLengths; ++h)
+      if (make_plan(h, &v.plan[v.count])) ++v.count;
     return v;
   }();
-  const auto it = std::lower_bound(plans.begin(), plans.end(), n_half,
-                                   [](const MixedPlan& p, int64_t h) { return p.n_half < h; });
-  return it != plans.end() && it->n_half == n_half ? &*it : nullptr;
+  const MixedPlan* end = plans.plan + plans.count;
+  const MixedPlan* it =
+      std::lower_bound(plans.plan, end, n_half, [](const MixedPlan& p, int64_t h) { return p.n_half < h; });
+  return it != end && it->n_half == n_half ? it : nullptr;
 }
 
 // In-place pairs <-> halfcomplex conversion of one row per workgroup (the permutation of

@@ -203,6 +203,14 @@ def test_bca_batched_validation(lib):
     assert lib.bca_backward_batched(2, xs, cs, gys, None, d, d, p, t, F32, None) == EINVAL
 
 
+def test_every_mixed_length_is_planned(lib):
+    """n/2 = 2^a 3^b 5^c up to 16384, no power of two: the table of plans holds all of them, and nothing else."""
+    mixed = {2**a * 3**b * 5**c for a in range(15) for b in range(10) for c in range(7)}
+    for h in range(1, 16385):
+        if h & (h - 1):
+            assert lib.rdfft_forward(None, 0, 2 * h, F32, None) == (OK if h in mixed else EUNSUP), h
+
+
 def test_bca_backward_keep_validation(lib):
     """gy is only read: it may share memory with x, dx may not be it, and long blocks are refused."""
     d, p, t = 256, 64, 8
