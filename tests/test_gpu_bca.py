@@ -70,6 +70,9 @@ SMALL = [
     (1, 4096, 4096, 4096, "bf16"),
     (1, 8192, 8192, 4096, "f32"),
     (1, 8192, 8192, 8192, "f16"),
+    # short batches with a ragged last tile
+    (82, 1536, 1536, 512, "f32"),
+    (177, 2048, 2048, 1024, "bf16"),
 ]
 
 
