@@ -438,11 +438,11 @@ constexpr int sq_bwd_wg() {
   using S = BcaSq<LOGN, QB, wg>;
   using S2 = BcaSq<LOGN, QB, 1024>;
   // Rows beyond a wave (blocks of 4096 and 8192): LDS holds one workgroup's tile whatever its
-  // size, and what bounds the kernel is VALU work (8192: 69 us of issue for 4096 tokens) with too few
-  // waves to reach it.  Sixteen waves instead of eight run a tile's forward transforms in half the
-  // rounds: bf16, 4096 tokens, one block of 8192 forward + backward 167 -> 159 us, backward of one
-  // block of 4096 67 -> 62 us and of 2 x 2 127 -> 117 us (float32: 78 and 162 us either way), in at most
-  // 128 registers.  Rows of one wave were slower (one block of 2048: 35 against 37 us).
+  // size, and eight waves are too few to keep the VALUs busy (8192, 4096 bf16 tokens: 77 us of VALU issue in
+  // a kernel of 112, a tenth of its waves' time in LDS waits, the rest of it barriers).  Sixteen waves run a
+  // tile's forward transforms in half the rounds: bf16, 4096 tokens, one block of 8192 forward + backward
+  // 167 -> 159 us, backward of one block of 4096 67 -> 62 us and of 2 x 2 127 -> 117 us (float32: 78 and 162 us
+  // either way), in at most 128 registers.  Rows of one wave were slower (one block of 2048: 35 against 37 us).
   if constexpr (BcaPlan<LOGN>::TPR > 64 && S::BT * S::NSL <= kSqMaxSlots) return 1024;
   return S::BT * S::NSL > kSqMaxSlots && S2::BT * S2::NSL <= kSqMaxSlots && BcaPlan<LOGN>::N <= 1024 ? 1024 : wg;
 }
