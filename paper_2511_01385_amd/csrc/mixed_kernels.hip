@@ -199,11 +199,13 @@ __device__ __forceinline__ float2 unit_root(int num, int den, float inv_den) {
 // Multiplies input r of a butterfly of radix R by w^r, w = exp(-+ 2 pi i k / (Ns R)), k < Ns.
 // Products carry a root's error once per factor: so w comes from Taylor sums in every storage type
 // (from radix 8 on it lies within 1/8 turn and needs no reduction), and from radix 6 on w^4 is a
-// root of its own, so that w^15 = (w^4)^3 w^3 has six errors, not fifteen.
+// root of its own, so that w^15 = (w^4)^3 w^3 has six errors, not fifteen: by Taylor sums too, but for
+// 16-bit rows of radix 9 and more, which the hardware functions serve within the old error (below) and 3 %
+// sooner.
 // (With the hardware functions for w and all powers from it, n = 6144 had a float32 error of 6.7e-7, and
 // 0.32 % of its float16 results fell on the wrong side of a rounding, plans of radices up to 8 before:
-// 4.3e-7 and 0.22 %; now 1.6e-7 and 0.13 %.  2^26 bf16 values, forward and inverse: 119 and 123 us.)
-template <bool INV, int R>
+// 4.3e-7 and 0.22 %; now 1.6e-7 and 0.15 %.  2^26 bf16 values, forward and inverse: 119 us then and now.)
+template <bool INV, int R, bool FINE>
 __device__ __forceinline__ void twiddle(float2* v, int k, int den, float inv_den) {
   float2 w[R];
   if constexpr (R < 8) {
@@ -212,7 +214,7 @@ __device__ __forceinline__ void twiddle(float2* v, int k, int den, float inv_den
     const float2 cs = cos_sin_quarters((float)(4 * k) * inv_den);
     w[1] = make_float2(cs.x, INV ? cs.y : -cs.y);
   }
-  if constexpr (R > 5) w[4] = unit_root<INV, true>(4 * k, den, inv_den);
+  if constexpr (R > 5) w[4] = unit_root<INV, FINE || R <= 8>(4 * k, den, inv_den);
   static_for<R - 1>([&](auto rc) {
     constexpr int r = decltype(rc)::value + 1;
     if constexpr (r == 2 || (r == 4 && R == 5) || r == 8) w[r] = c_mul<false>(w[r / 2], w[r / 2]);
@@ -240,6 +242,7 @@ constexpr int held_waves(int hold, bool inv) { return hold == kHoldOne ? 7 : hol
 template <int R, bool INV, int HOLD, bool FROM_GLOBAL, bool TO_GLOBAL, class Acc>
 __device__ __forceinline__ void mixed_pass(const MixedPass& p, int t, int tpr, bool active, float2* lds, const Acc& acc) {
   constexpr int MB = held(R, HOLD);
+  constexpr bool FINE = std::is_same<typename Acc::raw_t, float2>::value;
   float2 v[MB][R];
   int kk[MB], qq[MB];
 #pragma unroll
@@ -265,7 +268,7 @@ __device__ __forceinline__ void mixed_pass(const MixedPass& p, int t, int tpr, b
     const int j = t + s * tpr;
     if (j < p.B) {
       if constexpr (!FROM_GLOBAL) {
-        if (p.Ns > 1) twiddle<INV, R>(v[s], kk[s], p.Ns * R, p.inv_den);
+        if (p.Ns > 1) twiddle<INV, R, FINE>(v[s], kk[s], p.Ns * R, p.inv_den);
       }
       dft_any<R, INV>(v[s]);
       const int o = (j - kk[s]) * R + kk[s];
