@@ -390,7 +390,7 @@ bca_backward_block_kernel(const ElemOf<St>* __restrict__ x, const ElemOf<St>* __
         if (ij >= r0 && ij < r0 + nr) bca_lds[(ij - r0) * N + bin] = v;
       });
     __syncthreads();
-    atomic_add_rotated<WG, 1>(dc + (int64_t)r0 * 2 * N, reinterpret_cast<const float*>(bca_lds), nr * 2 * N);
+    atomic_add_rotated<WG, 1, 1>(dc + (int64_t)r0 * 2 * N, reinterpret_cast<const float*>(bca_lds), nr * 2 * N);
     __syncthreads();
   }
 }

@@ -61,11 +61,13 @@ extern __shared__ float2 bca_lds[];
 // cache lines, where the pairs' x and y parts one after the other touched four each, and the lines are
 // what the atomics wait for (4096-wide bf16 layer with dx over gy: 74 us by pairs).  Workgroup b
 // starts 128*b floats in, so that the workgroups, which all finish together, do not queue on the
-// same addresses, and four floats are in flight (2 x 2 blocks of 4096, 8 tokens: 21.0 -> 20.6 us).
-template <int WG, int COPIES>
+// same addresses, and four floats are in flight (2 x 2 blocks of 4096, 8 tokens: 21.0 -> 20.6 us); one is
+// better where a workgroup on every CU adds many rows (16 x 4 blocks of 256 in float16, 2045 tokens, the
+// matrix-core kernel forward + backward: 53.1 us with one, 53.7 with four).
+template <int WG, int COPIES, int UNROLL = 4>
 __device__ __forceinline__ void atomic_add_rotated(float* __restrict__ dst, const float* part, int count) {
   const int shift = (int)(((unsigned)blockIdx.x * 128u) % (unsigned)count);
-#pragma unroll 4
+#pragma unroll UNROLL
   for (int f0 = threadIdx.x; f0 < count; f0 += WG) {
     int f = f0 + shift;
     if (f >= count) f -= count;
