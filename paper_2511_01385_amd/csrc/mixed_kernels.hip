@@ -6,12 +6,12 @@
 // inverse pre-pass (1/n folded in) followed by the conjugate passes.  A row's N complex
 // points pass through LDS between Stockham passes whose radices (up to 16: the composite 6,
 // 9, 10, 12 and 15 beside the powers of two) a host plan picks at run time; a butterfly's first
-// and fourth twiddle powers come from Taylor sums of sine and cosine and the others from products,
-// so these plans need no table.
+// and fourth twiddle powers come from Taylor sums of sine and cosine (the fourth of 16-bit rows, at
+// radix 9 and more, from the hardware functions) and the others from products, so these plans need no table.
 //
 // What bounds them: VALU work and the waits between passes in 16-bit storage, HBM in float32.
-// n = 6144 (16 16 12, 12 points a thread, about 1010 VALU instructions per wave), 16384 rows, takes 99
-// us forward and 117 us inverse in bf16 (4.1 and 3.4 TB/s), 149 us each in float32 (5.4 TB/s).  Radices up to
+// n = 6144 (16 16 12, 12 points a thread, about 1010 VALU instructions per wave), 16384 rows, takes 95
+// us forward and 113 us inverse in bf16 (4.2 and 3.6 TB/s), 149 us each in float32 (5.4 TB/s).  Radices up to
 // 8, always 16 points per thread and the row staged through LDS before its
 // first and after its last pass (five passes, 1740 instructions for 16 points) took 200 and 208 us,
 // 231 and 192 us; 65536 rows of n = 96, each in a workgroup of its own then, 48 us against 9 us.
@@ -178,8 +178,9 @@ __device__ __forceinline__ float2 cos_sin_quarters(float f) {
   return make_float2(c, s);
 }
 
-// exp(-+ 2 pi i num / den) for 0 <= num < den; the caller passes inv_den = 1/den.  FINE: the angle is reduced to |f| <= 1/2 quarter turns in integers, so that its rounding is
-// relative to f.  Else the hardware sine and cosine of the angle in revolutions, a few 1e-7 off.
+// exp(-+ 2 pi i num / den) for 0 <= num < den; the caller passes inv_den = 1/den.  FINE: the angle
+// is reduced to |f| <= 1/2 quarter turns in integers, so that its rounding is relative to f.  Else the
+// hardware sine and cosine of the angle in revolutions, a few 1e-7 off.
 template <bool INV, bool FINE>
 __device__ __forceinline__ float2 unit_root(int num, int den, float inv_den) {
   if constexpr (FINE) {
